@@ -572,8 +572,10 @@ __global__ __launch_bounds__(C::THREADS) void wino_tap_gemm(const int8_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// K2R wino_tap_gemm_rows: the same contraction with the output transform
-// folded in row by row.
+// K2R: the same contraction with the output transform folded in row by row.
+// wino_tap_gemm_rows (wino_tap_rows.h) is the kernel that runs by default on
+// large layers; the constants here are shared with it.  The body below serves
+// its stream-K variant wino_tap_gemm_rows_sk (forced only).
 //
 // Y = A^T M' A is linear in the taps, and its row pass only mixes the six
 // taps of one row a of the 6x6 tile: Y = sum_a A^T[:, a] (M'[a, :] A).  So the
@@ -589,8 +591,7 @@ __global__ __launch_bounds__(C::THREADS) void wino_tap_gemm(const int8_t* __rest
 // of 64 Uq rows + 64 Vq rows, 8 KB each; three stages rotate through 144 KB
 // of LDS, two in flight.  The 16 waves form 4 (channels) x 4 (tiles), one
 // 16x16x64 MFMA block each: 16 + 6 values per pair is 88 registers a lane,
-// which fits the 128 a wave has at four waves per SIMD.  (Two blocks per
-// wave at eight waves would need 176 of 256 and the compiler spills.)
+// which fits the 128 a wave has at four waves per SIMD.
 // A slice is 8 groups of 16 rows; wave w copies group w % 8 of the slices
 // b = w / 8, w / 8 + 2, w / 8 + 4 (groups 0-3: Uq, 4-7: Vq), so its loads
 // never branch.
@@ -719,21 +720,21 @@ __device__ __forceinline__ int sk_owner(int u, const K2Args& g) {
     return c;
 }
 
-// The row-streamed kernel's body; SK: with the stream-K split (the kernel
-// wino_tap_gemm_rows_sk), else every workgroup runs one whole block.
-template <int LAYOUT, bool SK>
-__device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq, const int8_t* __restrict__ vq,
-                                                   const int32_t* __restrict__ bias, int8_t* __restrict__ y,
-                                                   const K2Args& g) {
+// The stream-K kernel: workgroups below n_dp run a whole block each, the rest
+// their share of the split blocks' stages.
+template <int LAYOUT>
+__global__ __launch_bounds__(KR_THREADS) void wino_tap_gemm_rows_sk(const int8_t* __restrict__ uq,
+                                                                    const int8_t* __restrict__ vq,
+                                                                    const int32_t* __restrict__ bias,
+                                                                    int8_t* __restrict__ y, K2Args g) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[KR_NBUF * KR_STAGE];
     __shared__ __attribute__((aligned(16))) int bias_blk[KR_CO];
     __shared__ int sk_last;
     // the alignment shifts of the split kernel, read per row fold (from the
     // kernel arguments the compiler would keep all 36 in scalar registers
     // across its pieces)
-    __shared__ int sh_tab[SK ? kTaps : 1];
-    if constexpr (SK)
-        if (threadIdx.x < kTaps) sh_tab[threadIdx.x] = g.tab.sh[threadIdx.x];
+    __shared__ int sh_tab[kTaps];
+    if (threadIdx.x < kTaps) sh_tab[threadIdx.x] = g.tab.sh[threadIdx.x];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cw = wave & 3, tw = wave >> 2;
@@ -742,7 +743,7 @@ __device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq
     const int nstage = 6 * nkc;
 
     // stream-K workgroup index (-1: a whole block)
-    const int sk = !SK || (int)blockIdx.x < g.n_dp ? -1 : xcd_remap((int)blockIdx.x - g.n_dp, g.sk_groups);
+    const int sk = (int)blockIdx.x < g.n_dp ? -1 : xcd_remap((int)blockIdx.x - g.n_dp, g.sk_groups);
 
     // copy side, fixed parts: this wave's 16 rows, this lane's 16 bytes of
     // slices b0, b0 + step, ... of a stage (k-blocked operands
@@ -886,7 +887,7 @@ __device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq
                 for (int r = 0; r < 4; ++r) {
                     int mv[6], z[4];
 #pragma unroll
-                    for (int b = 0; b < 6; ++b) mv[b] = m[b][tb][r] << (SK ? sh_tab[6 * a + b] : g.tab.sh[6 * a + b]);
+                    for (int b = 0; b < 6; ++b) mv[b] = m[b][tb][r] << sh_tab[6 * a + b];
                     if (a == 1) mv[1] += bias_rnd[r];
                     at_1d(mv, z);
                     int* yr = yv[tb][r];
@@ -912,7 +913,7 @@ __device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq
                     for (int p = 0; p < 16; ++p) asm volatile("" : "+v"(yv[tb][r][p]));
         }
 
-        if (SK && (sb != 0 || se != nstage)) {
+        if (sb != 0 || se != nstage) {
             // a piece of a split block: finish the block or leave a partial Y
             const int jb = (lbid - g.n_dp) * nstage;   // its first stage in the split sequence
             const int glo = sk_owner(jb, g), ghi = sk_owner(jb + nstage - 1, g);
@@ -1008,7 +1009,7 @@ __device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq
     // Whole blocks and the (at most two) pieces of a stream-K range each take
     // a copy of the piece code: as a loop over pieces, the compiler kept the
     // loop-invariant scalars of the whole body live across it and spilled.
-    if (!SK || sk < 0) {
+    if (sk < 0) {
         piece(xcd_remap(blockIdx.x, g.n_dp), 0, nstage, true);
         return;
     }
@@ -1031,22 +1032,7 @@ __device__ __forceinline__ void tap_gemm_rows_body(const int8_t* __restrict__ uq
     }
 }
 
-template <int LAYOUT>
-__global__ __launch_bounds__(KR_THREADS) void wino_tap_gemm_rows(const int8_t* __restrict__ uq,
-                                                                 const int8_t* __restrict__ vq,
-                                                                 const int32_t* __restrict__ bias,
-                                                                 int8_t* __restrict__ y, K2Args g) {
-    tap_gemm_rows_body<LAYOUT, false>(uq, vq, bias, y, g);
-}
-
-template <int LAYOUT>
-__global__ __launch_bounds__(KR_THREADS) void wino_tap_gemm_rows_sk(const int8_t* __restrict__ uq,
-                                                                    const int8_t* __restrict__ vq,
-                                                                    const int32_t* __restrict__ bias,
-                                                                    int8_t* __restrict__ y, K2Args g) {
-    tap_gemm_rows_body<LAYOUT, true>(uq, vq, bias, y, g);
-}
-
+#include "wino_tap_rows.h"
 #include "wino_tap_ws.h"
 
 // ---------------------------------------------------------------------------
@@ -1569,12 +1555,17 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
                 else
                     hipLaunchKernelGGL(wino_tap_gemm_rows_sk<WINO_NCHW>, dim3(grid), dim3(KR_THREADS), 0, stream,
                                        p->uq_dev, vq, p->bias_dev, y, a);
-            } else if (layout == WINO_NHWC) {
-                hipLaunchKernelGGL(wino_tap_gemm_rows<WINO_NHWC>, dim3(grid), dim3(KR_THREADS), 0, stream, p->uq_dev,
-                                   vq, p->bias_dev, y, a);
             } else {
-                hipLaunchKernelGGL(wino_tap_gemm_rows<WINO_NCHW>, dim3(grid), dim3(KR_THREADS), 0, stream, p->uq_dev,
-                                   vq, p->bias_dev, y, a);
+#define RW_LAUNCH(L, ONE)                                                                                        \
+    hipLaunchKernelGGL((wino_tap_gemm_rows<L, ONE>), dim3(grid), dim3(RW_THREADS), 0, stream, p->uq_dev, vq, p->bias_dev, \
+                       y, a)
+                const bool one = p->cin_pad == kKStep;
+                if (layout == WINO_NHWC) {
+                    if (one) RW_LAUNCH(WINO_NHWC, true); else RW_LAUNCH(WINO_NHWC, false);
+                } else {
+                    if (one) RW_LAUNCH(WINO_NCHW, true); else RW_LAUNCH(WINO_NCHW, false);
+                }
+#undef RW_LAUNCH
             }
             return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
         }

@@ -1,0 +1,373 @@
+// Tap GEMM + output transform for F(4x4,3x3), int8 operands, 32-bit
+// epilogue: the row-streamed kernel wino_tap_gemm_rows.  Included by
+// wino_kernels.hip inside its anonymous namespace.
+//
+// Y = A^T M' A is linear in the taps, and its row pass only mixes the six
+// taps of one row a of the 6x6 tile: with z_a = (M'[a, :]) A, Y = sum_a
+// A^T[:, a] z_a.  So the taps stream row by row: the six M_t of row a
+// accumulate over all input channels, fold into z_a, and their accumulators
+// serve the next row.
+//
+// Order of the rows.  Columns 1 and 2 of A^T (and 3 and 4) differ only in the
+// signs of the odd output rows, so rows 1 and 2 enter Y as p = z1 + z2 (even
+// output rows) and m = z1 - z2 (odd ones), rows 3 and 4 as q = z3 + z4 and
+// r = z3 - z4:
+//   Y0 = z0 + p + q, Y1 = m + 2 r, Y2 = p + 4 q, Y3 = z5 + m + 8 r.
+// Taken as 1, 2, 3, 4, 0, 5, a (tile, channel) pair keeps p and m (8 values),
+// then z3 beside them; after row 4 the output rows 1 and 2 are final and are
+// requantized to packed bytes at once, p + q and m + 8 r remain, and rows 0
+// and 5 finish output rows 0 and 3.  That is 12 int32 per pair at the most
+// next to the row's six accumulators, where adding every z_a into a 4x4 Y
+// needs 16, and 16 additions per row pair instead of 32.
+//
+// Integer arithmetic is exact: the 32-bit epilogue is only selected when the
+// plan's bound on the sum of the terms' magnitudes, which bounds every
+// partial sum above, is below 2^31.
+constexpr int RW_CB = 2;                                  // 16-channel blocks per wave
+constexpr int RW_WAVES = 16 / RW_CB;                      // 2 (channels) x 4 (tiles) blocks of 32 x 16
+constexpr int RW_THREADS = 64 * RW_WAVES;
+constexpr int RW_LPW = KR_STAGE / 1024 / RW_WAVES;        // 1-KB loads per wave per stage
+constexpr int RW_V = 4 * RW_CB;                           // pairs per lane
+static_assert(KR_CO == 64 && KR_TL == 64 && RW_CB * RW_WAVES == 16, "the waves' blocks tile the workgroup block");
+static_assert(RW_WAVES == 8, "wave -> copied row group map");
+static_assert((KR_NBUF - 2) * RW_LPW <= 63, "vmcnt range");
+
+struct NoFold {
+    __device__ __forceinline__ void operator()(int) const {}
+};
+enum { RW_NONE, RW_COPY, RW_ASK };
+
+// global -> LDS copy of 16 bytes per lane as lds_copy16, with the address as
+// a wave-uniform 64-bit base and a 32-bit lane offset.  No memory clobber: the
+// ring's barriers order it against the LDS reads of its buffer, and reads of
+// the other buffers may move across it.
+__device__ __forceinline__ void lds_copy16_s(const void* base, uint32_t lane_off,
+                                             __attribute__((address_space(3))) void* dst) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "{m0}"(m0));
+}
+
+// two int32 (rounding constant included) -> clamp(v >> s, -128, 127), packed
+// in the low half; two such halves -> one word
+__device__ __forceinline__ uint32_t requant2(int a, int b, int s) {
+    return __builtin_amdgcn_ashr_pk_i8_i32(a, b, s);
+}
+__device__ __forceinline__ uint32_t join2(uint32_t lo, uint32_t hi) {
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+// max(byte, 0) of the four signed bytes of w
+__device__ __forceinline__ uint32_t relu4(uint32_t w) {
+    const uint32_t t = w & 0x80808080u;
+    return w & ~(t | (t - (t >> 7)));
+}
+
+template <int LAYOUT, bool ONE>
+__global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
+    const int8_t* __restrict__ uq, const int8_t* __restrict__ vq, const int32_t* __restrict__ bias,
+    int8_t* __restrict__ y, K2Args g) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[KR_NBUF * KR_STAGE];
+    __shared__ __attribute__((aligned(16))) int bias_blk[KR_CO];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cw = wave & 1, tw = wave >> 1;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int nkc = g.cin_pad / kKStep;
+    const int nstage = 6 * nkc;
+    const int lbid = xcd_remap(blockIdx.x, g.nblocks);
+    const int bco = lbid % g.nbco, btl = lbid / g.nbco;
+    const int co_blk = bco * KR_CO;
+    const long long tl_blk = (long long)btl * KR_TL;
+    // the block's bias into LDS as the first copy of the ring, which the wait
+    // for stage 0 covers (vmcnt counts in order): loaded through a register, it
+    // would hold the ring's start up for a memory round trip
+    if (wave == 0) {
+        const uint32_t m0 = __builtin_amdgcn_readfirstlane(
+            (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)bias_blk);
+        asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(4 * lane), "s"(bias + co_blk), "{m0}"(m0)
+                     : "memory");
+    }
+
+    // copy side: wave w copies row group w (16 rows; 0-3: Uq, 4-7: Vq) of each
+    // of a stage's six slices (k-blocked operands
+    // Uq[36][cin_pad/64][cout_pad][64], Vq[36][cin_pad/64][t_pad][64])
+    const int rr = lane >> 2;
+    const uint32_t lane_off = (uint32_t)(rr * 64 + 16 * lds_slot(rr, lane & 3));
+    const bool copies_u = wave < 4;
+    const long long rows = copies_u ? (long long)g.cout_pad : g.t_pad;
+    const long long tap_stride = rows * g.cin_pad, kc_stride = rows * kKStep;
+    const int8_t* const src0 = copies_u ? uq + (long long)(co_blk + 16 * wave) * kKStep
+                                        : vq + (tl_blk + 16 * (wave - 4)) * kKStep;
+    constexpr uint32_t kRowOrder = 0x504321u;             // rows of taps in stream order, 4 bits each
+    const int8_t* next_src = src0 + 6 * tap_stride;
+    uint32_t rows_left = kRowOrder >> 4;
+    int next_kc = 0, next_buf = 0;
+    auto issue_slice = [&](int b) __attribute__((always_inline)) {
+        lds_copy16_s(next_src + b * tap_stride, lane_off,
+                     (__attribute__((address_space(3))) void*)(lds + next_buf * KR_STAGE + 1024 * wave + b * KR_CHUNK));
+    };
+    auto issue_end = [&]() __attribute__((always_inline)) {
+        if (++next_kc == nkc) {
+            next_kc = 0;
+            next_src = src0 + (long long)(6 * (int)(rows_left & 15)) * tap_stride;
+            rows_left >>= 4;
+        } else {
+            next_src += kc_stride;
+        }
+        next_buf = next_buf == KR_NBUF - 1 ? 0 : next_buf + 1;
+    };
+    auto issue_next = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 6; ++b) issue_slice(b);
+        issue_end();
+    };
+
+    // compute side: fragment offsets within a slice
+    const int row_a = 16 * RW_CB * cw + lr, row_b = KR_CO + 16 * tw + lr;
+    const int frag_a = row_a * 64 + 16 * lds_slot(row_a, lk);   // block c: + 16 c rows
+    const int frag_b = row_b * 64 + 16 * lds_slot(row_b, lk);
+    const int rnd = g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
+
+    // value k = 4 c + r of a lane: channel 16 (RW_CB cw + c) + 4 lk + r of tile
+    // 16 tw + lr
+    int P[RW_V][4], Q[RW_V][4], Z[RW_V][4];
+    uint32_t out[4][RW_V];                                 // packed bytes
+    // A finished output row i arrives value by value, v = its four pixels of
+    // channel r of block c.  NHWC: word 4 c + j = channels r = 0..3 of pixel
+    // (i, j), packed pair by pair; NCHW: word 4 c + r = the pixels of channel r.
+    int prev[2][4];
+    uint32_t half[2][4];
+    auto put = [&](int i, int slot, int c, int r, const int (&v)[4]) __attribute__((always_inline)) {
+        if (LAYOUT == WINO_NCHW) {
+            out[i][4 * c + r] = join2(requant2(v[0], v[1], g.out_shift), requant2(v[2], v[3], g.out_shift));
+            asm volatile("" : "+v"(out[i][4 * c + r]));
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (r == 0 || r == 2) prev[slot][j] = v[j];
+            if (r == 1) half[slot][j] = requant2(prev[slot][j], v[j], g.out_shift);
+            if (r == 3) {
+                out[i][4 * c + j] = join2(half[slot][j], requant2(prev[slot][j], v[j], g.out_shift));
+                asm volatile("" : "+v"(out[i][4 * c + j]));
+            }
+        }
+    };
+    // fold value 4 c + r of the finished row a of taps, accumulators m.  The
+    // empty asm statements pin the results: they are read much later, and the
+    // compiler would sink the folds past the next rows and keep all their
+    // accumulators live.
+    v4i bias_rnd;
+    auto fold = [&](auto row_a, v4i (&m)[6][RW_CB], int c, int r) __attribute__((always_inline)) {
+        constexpr int a = decltype(row_a)::value;
+        const int k = 4 * c + r;
+        int mv[6], z[4];
+#pragma unroll
+        for (int b = 0; b < 6; ++b) mv[b] = m[b][c][r] << g.tab.sh[6 * a + b];
+        if (a == 1) {
+            // bias plus rounding constant, injected through tap (1,1): its row
+            // and column of A^T are all ones, so it reaches every output of
+            // the tile once
+            if (r == 0) bias_rnd = *(const v4i*)(bias_blk + 16 * (RW_CB * cw + c) + 4 * lk) + rnd;
+            mv[1] += bias_rnd[r];
+        }
+        at_1d(mv, z);
+        int y1[4], y2[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (a == 1 || a == 3) Z[k][j] = z[j];
+            if (a == 2) {
+                P[k][j] = Z[k][j] + z[j];
+                Q[k][j] = Z[k][j] - z[j];
+            }
+            if (a == 4) {
+                const int qv = Z[k][j] + z[j], rv = Z[k][j] - z[j];
+                y1[j] = Q[k][j] + (rv << 1);
+                y2[j] = P[k][j] + (qv << 2);
+                P[k][j] += qv;
+                Q[k][j] += rv << 3;
+            }
+            if (a == 0) P[k][j] += z[j];
+            if (a == 5) Q[k][j] += z[j];
+            if (a == 1 || a == 3) asm volatile("" : "+v"(Z[k][j]));
+            if (a == 2 || a == 4) asm volatile("" : "+v"(P[k][j]), "+v"(Q[k][j]));
+        }
+        if (a == 4) {
+            put(1, 0, c, r, y1);
+            put(2, 1, c, r, y2);
+        }
+        if (a == 0) put(0, 0, c, r, P[k]);
+        if (a == 5) put(3, 0, c, r, Q[k]);
+    };
+
+    issue_next();
+    if (nstage > 1) issue_next();
+    int s = 0, buf = 0;
+    // One stage: six taps x 64 input channels into the row's accumulators m
+    // (from zero if FIRST).  fold_r(r), r = 0..3, folds part of the row before
+    // by VALU instructions between this stage's MFMAs: both waves of a SIMD
+    // are in the same phase, so a fold after the row's last stage would leave
+    // the matrix cores idle.
+    // COPY: whether the copies of stage s + 2 go out (RW_COPY), there is no
+    // such stage (RW_NONE), or that depends on s (RW_ASK).  Only the last row
+    // has to ask (with one 64-channel chunk, the last two have none), and
+    // without the branches a stage is one block for the scheduler.
+    auto stage = [&](auto first, auto copy, auto fold_r, v4i (&m)[6][RW_CB]) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first)::value;
+        constexpr int COPY = decltype(copy)::value;
+        // stage s has landed once only the next stage's loads are pending
+        if (COPY == RW_COPY || s + 1 < nstage)
+            WINO_WAIT_VM_LDS(RW_LPW);
+        else
+            WINO_WAIT_VM_LDS(0);
+        ring_barrier();   // stage s visible; stage s-1 (same buffer as s+2) consumed
+        // Stage s+2's copies go out one slice per tap, between the MFMAs: a
+        // copy instruction holds its wave while the load path is busy (64 B/clk
+        // per CU, 16 clk and more for each), and the six in a row kept every
+        // wave from computing for 400-700 of a stage's 1430 clk.
+        const bool more = COPY == RW_COPY || (COPY == RW_ASK && s + 2 < nstage);
+        const uint8_t* base = lds + buf * KR_STAGE;
+        buf = buf == KR_NBUF - 1 ? 0 : buf + 1;
+        ++s;
+        // fragments of two taps in flight ahead of the MFMAs
+        v4i fa[2][RW_CB], fb[2];
+        auto frag = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < RW_CB; ++c)
+                fa[b & 1][c] = *(const v4i*)(base + b * KR_CHUNK + frag_a + 1024 * c);
+            fb[b & 1] = *(const v4i*)(base + b * KR_CHUNK + frag_b);
+        };
+        frag(0);
+        frag(1);
+        const v4i zero = (v4i){0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+#pragma unroll
+            for (int c = 0; c < RW_CB; ++c)
+                m[b][c] =
+                    __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[b & 1][c], fb[b & 1], FIRST ? zero : m[b][c], 0, 0, 0);
+            if (more) issue_slice(b);
+            if (b + 2 < 6) frag(b + 2);
+            if (b > 0 && b < 5) fold_r(b - 1);
+            __builtin_amdgcn_sched_barrier(0);     // the taps' parts stay apart
+        }
+        if (more) issue_end();
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    // row of taps: accumulators m, f(c, r) folds the row before
+    auto row = [&](v4i (&m)[6][RW_CB], auto copy, auto f) __attribute__((always_inline)) {
+        if constexpr (ONE) {
+            stage(yes, copy, [&](int r) __attribute__((always_inline)) {
+                f(r >> 1, 2 * (r & 1));
+                f(r >> 1, 2 * (r & 1) + 1);
+            }, m);
+        } else {
+            stage(yes, copy, [&](int r) __attribute__((always_inline)) { f(0, r); }, m);
+            stage(no, copy, [&](int r) __attribute__((always_inline)) { f(1, r); }, m);
+            for (int kc = 2; kc < nkc; ++kc) stage(no, copy, NoFold{}, m);
+        }
+    };
+    const std::integral_constant<int, RW_COPY> copy;
+    const std::integral_constant<int, ONE ? RW_NONE : RW_COPY> copy4;
+    const std::integral_constant<int, ONE ? RW_NONE : RW_ASK> copy5;
+    v4i ma[6][RW_CB], mb[6][RW_CB];
+#define RW_ROW(m, cp, mp, prev) \
+    row(m, cp, [&](int c, int r) __attribute__((always_inline)) { fold(std::integral_constant<int, prev>{}, mp, c, r); })
+    stage(yes, copy, NoFold{}, ma);
+    if constexpr (!ONE)
+        for (int kc = 1; kc < nkc; ++kc) stage(no, copy, NoFold{}, ma);
+    RW_ROW(mb, copy, ma, 1);
+    RW_ROW(ma, copy, mb, 2);
+    RW_ROW(mb, copy, ma, 3);
+    RW_ROW(ma, copy4, mb, 4);
+    RW_ROW(mb, copy5, ma, 0);
+#undef RW_ROW
+#pragma unroll
+    for (int k = 0; k < RW_V; ++k) fold(std::integral_constant<int, 5>{}, mb, k >> 2, k & 3);
+    if (g.relu)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < RW_V; ++k) out[i][k] = relu4(out[i][k]);
+
+    if constexpr (LAYOUT == WINO_NHWC) {
+        // gather the block's output in LDS (the ring is idle now) so that
+        // every pixel's 64 channel bytes leave together
+        constexpr int PITCH = 16 * 64 + 16;   // bytes per tile; the pad spreads lanes over banks
+        static_assert(KR_TL * PITCH <= KR_NBUF * KR_STAGE, "output staging fits the ring");
+        __syncthreads();                      // every wave is done reading the ring
+        uint8_t* ot = lds + (16 * tw + lr) * PITCH + 16 * RW_CB * cw + 4 * lk;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < RW_CB; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) *(uint32_t*)(ot + 64 * (4 * i + j) + 16 * c) = out[i][4 * c + j];
+        __syncthreads();
+        if (g.y_staged) {
+            // wave w stores tiles w, w + 8, ...: lane = 16-byte quarter q of
+            // pixel p; all LDS reads first, so that they overlap
+            const int p = lane >> 2, q = lane & 3;
+            constexpr int NT = KR_TL / RW_WAVES;
+            v4i d[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                d[i] = *(const v4i*)(lds + (wave + RW_WAVES * i) * PITCH + 64 * p + 16 * q);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const long long tile = tl_blk + wave + RW_WAVES * i;   // wave-uniform
+                if (tile >= g.ntiles) break;
+                int img, ty, tx;
+                tile_coords(tile, g, img, ty, tx);
+                const int yy = 4 * ty + (p >> 2), xx = 4 * tx + (p & 3);
+                // non-temporal: the output is not read again here, and in L2
+                // it would evict the operands the next round of blocks reads
+                // (measured 2-3% of the kernel at C5 and C4)
+                if (yy < g.h && xx < g.w)
+                    __builtin_nontemporal_store(
+                        d[i], (v4i*)(y + (((long long)img * g.h + yy) * g.w + xx) * g.cout + co_blk + 16 * q));
+            }
+        } else {
+            // any Cout and alignment: lane = channel, one pixel per store
+            const int co = co_blk + lane;
+            for (int tl = wave; tl < KR_TL; tl += RW_WAVES) {
+                const long long tile = tl_blk + tl;
+                if (tile >= g.ntiles) break;
+                int img, ty, tx;
+                tile_coords(tile, g, img, ty, tx);
+                for (int p = 0; p < 16; ++p) {
+                    const int yy = 4 * ty + (p >> 2), xx = 4 * tx + (p & 3);
+                    if (yy < g.h && xx < g.w && co < g.cout)
+                        y[(((long long)img * g.h + yy) * g.w + xx) * g.cout + co] =
+                            (int8_t)lds[tl * PITCH + 64 * p + lane];
+                }
+            }
+        }
+    } else {
+        const long long tile = tl_blk + 16 * tw + lr;
+        if (tile >= g.ntiles) return;
+        int img, ty, tx;
+        tile_coords(tile, g, img, ty, tx);
+        const bool word = (g.w & 3) == 0 && ((uintptr_t)y & 3) == 0;
+#pragma unroll
+        for (int c = 0; c < RW_CB; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int co = co_blk + 16 * (RW_CB * cw + c) + 4 * lk + r;
+                if (co >= g.cout) continue;
+                int8_t* base = y + (((long long)img * g.cout + co) * g.h + 4 * ty) * g.w + 4 * tx;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (4 * ty + i >= g.h) continue;
+                    const uint32_t w = out[i][4 * c + r];
+                    if (word) {
+                        *(uint32_t*)(base + (long long)i * g.w) = w;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (4 * tx + j < g.w) base[(long long)i * g.w + j] = (int8_t)(w >> (8 * j));
+                    }
+                }
+            }
+    }
+}
