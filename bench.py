@@ -480,7 +480,7 @@ def main():
     elif choice == W.TAP_ROWS_STREAMK:
         k2_name, k2_inst = "wino_tap_gemm_rows_sk", f"wino_tap_gemm_rows_sk<{lay}>"
     elif rows:
-        k2_name, k2_inst = "wino_tap_gemm_rows", f"wino_tap_gemm_rows<{lay},{'true' if cin <= 64 else 'false'}>"
+        k2_name, k2_inst = "wino_tap_gemm_rows", "wino_tap_gemm_rows<RwCfg<%s>,%d,%s>" % (("32,3,4", lay, "true") if cin <= 64 else ("64,6,3", lay, "false"))
     elif choice == W.TAP_WAVES:
         # 64-channel chunks per ring stage: the largest of 4, 3, 2, 1 dividing the padded chunks
         nkc = (cin + 63) // 64

@@ -1033,6 +1033,7 @@ __global__ __launch_bounds__(KR_THREADS) void wino_tap_gemm_rows_sk(const int8_t
 }
 
 #include "wino_tap_rows.h"
+#include "wino_tap_small.h"
 #include "wino_tap_ws.h"
 
 // ---------------------------------------------------------------------------
@@ -1390,6 +1391,32 @@ int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     return WINO_TAP_RESIDENT_64X32;
 }
 
+// The row-streamed kernel's block and ring, by the input channels.  With one
+// 64-channel chunk a block has only six rows of six taps to run: two 64 x 32
+// workgroups per CU, one starting or storing while the other computes
+// (1x64->64 568x568: 20.0 us against 24.9 with 64 x 64 blocks).  From two
+// chunks on the operand copies bound the kernel, and a 64 x 64 block moves two
+// thirds of the bytes per multiply-add (128 channels, 256x512: 16.9 against
+// 18.4 us; 256 channels, 4x160x160: 39.4 against 44.8).  64 x 64 with half-row
+// stages, six in the ring: 18.5 and 44.1 us.
+using RwNarrow = RwCfg<32, 3, 4>;
+using RwWide = RwCfg<64, 6, 3>;
+
+template <class C, bool ONE>
+wino_status launch_rows(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
+                        K2Args a, hipStream_t stream) {
+    const long long nb = (long long)(p->cout_pad / RW_CO) * ((g.ntiles + C::TL - 1) / C::TL);
+    if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
+    a.nblocks = (int)nb;
+    if (layout == WINO_NHWC)
+        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NHWC, ONE>), dim3((unsigned)nb), dim3(C::THREADS), 0, stream,
+                           p->uq_dev, vq, p->bias_dev, y, a);
+    else
+        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NCHW, ONE>), dim3((unsigned)nb), dim3(C::THREADS), 0, stream,
+                           p->uq_dev, vq, p->bias_dev, y, a);
+    return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+}
+
 // 64-channel chunks per ring stage of the wave-specialized kernel: the
 // largest of 4, 3, 2, 1 that divides the padded input channels' chunks
 int ws_chunks_per_stage(int cin_pad) {
@@ -1482,6 +1509,25 @@ wino_status launch_rows_wide(const wino_f4_plan_s* p, const Geometry& g, wino_la
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
+template <int M, int CB, int TB>
+wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
+                         K2Args a, hipStream_t stream) {
+    a.nbco = p->cout_pad / (16 * CB);
+    const int nco = (p->cout + 16 * CB - 1) / (16 * CB);   // blocks that hold channels
+    a.nbco = nco;
+    const long long nb = (long long)nco * ((g.ntiles + 16 * TB - 1) / (16 * TB));
+    if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
+    a.nblocks = (int)nb;
+    if (layout == WINO_NHWC)
+        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NHWC>), dim3((unsigned)nb), dim3(64 * (M + 2)), 0,
+                           stream, p->uq_dev, vq, p->bias_dev, y, a);
+    else
+        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NCHW>), dim3((unsigned)nb), dim3(64 * (M + 2)), 0,
+                           stream, p->uq_dev, vq, p->bias_dev, y, a);
+    return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+}
+int small_shape() { static const char* e = getenv("TS"); return e ? atoi(e) : 0; }
+
 // ws_bytes: the workspace at vq (the stream-K split uses the part past Vq)
 template <int MODE>
 wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
@@ -1530,6 +1576,15 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
         }
         return launch_resident<K2Mid10, 4, MODE, 10>(p, g, layout, vq, y, aux, a, stream);
     }
+    if (MODE == 0 && p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO && small_shape() &&
+        (p->m == 2 || tap_kernel_for(p, g, MODE) != WINO_TAP_ROWS || small_shape() > 100)) {
+        switch (small_shape() % 100) {
+            case 11: return p->m == 2 ? launch_small<2, 1, 1>(p, g, layout, vq, y, a, stream) : launch_small<4, 1, 1>(p, g, layout, vq, y, a, stream);
+            case 12: return p->m == 2 ? launch_small<2, 1, 2>(p, g, layout, vq, y, a, stream) : launch_small<4, 1, 2>(p, g, layout, vq, y, a, stream);
+            case 21: return p->m == 2 ? launch_small<2, 2, 1>(p, g, layout, vq, y, a, stream) : launch_small<4, 2, 1>(p, g, layout, vq, y, a, stream);
+            case 22: return p->m == 2 ? launch_small<2, 2, 2>(p, g, layout, vq, y, a, stream) : launch_small<4, 2, 2>(p, g, layout, vq, y, a, stream);
+        }
+    }
     if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
     switch (tap_kernel_for(p, g, MODE)) {
         case WINO_TAP_ROWS: {
@@ -1555,19 +1610,10 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
                 else
                     hipLaunchKernelGGL(wino_tap_gemm_rows_sk<WINO_NCHW>, dim3(grid), dim3(KR_THREADS), 0, stream,
                                        p->uq_dev, vq, p->bias_dev, y, a);
-            } else {
-#define RW_LAUNCH(L, ONE)                                                                                        \
-    hipLaunchKernelGGL((wino_tap_gemm_rows<L, ONE>), dim3(grid), dim3(RW_THREADS), 0, stream, p->uq_dev, vq, p->bias_dev, \
-                       y, a)
-                const bool one = p->cin_pad == kKStep;
-                if (layout == WINO_NHWC) {
-                    if (one) RW_LAUNCH(WINO_NHWC, true); else RW_LAUNCH(WINO_NHWC, false);
-                } else {
-                    if (one) RW_LAUNCH(WINO_NCHW, true); else RW_LAUNCH(WINO_NCHW, false);
-                }
-#undef RW_LAUNCH
+                return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
             }
-            return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+            return p->cin_pad == kKStep ? launch_rows<RwNarrow, true>(p, g, layout, vq, y, a, stream)
+                                        : launch_rows<RwWide, false>(p, g, layout, vq, y, a, stream);
         }
         case WINO_TAP_WAVES: {
             const long long wblocks = (long long)(p->cout_pad / WS_CO) * (g.t_pad / WS_TL);

@@ -24,18 +24,25 @@
 // plan's bound on the sum of the terms' magnitudes, which bounds every
 // partial sum above, is below 2^31.
 constexpr int RW_CB = 2;                                  // 16-channel blocks per wave
-constexpr int RW_WAVES = 16 / RW_CB;                      // 2 (channels) x 4 (tiles) blocks of 32 x 16
-constexpr int RW_THREADS = 64 * RW_WAVES;
-constexpr int RW_LPW = KR_STAGE / 1024 / RW_WAVES;        // 1-KB loads per wave per stage
+constexpr int RW_CO = 64;
 constexpr int RW_V = 4 * RW_CB;                           // pairs per lane
-static_assert(KR_CO == 64 && KR_TL == 64 && RW_CB * RW_WAVES == 16, "the waves' blocks tile the workgroup block");
-static_assert(RW_WAVES == 8, "wave -> copied row group map");
-static_assert((KR_NBUF - 2) * RW_LPW <= 63, "vmcnt range");
-
-struct NoFold {
-    __device__ __forceinline__ void operator()(int) const {}
+// Block of 64 channels x TL tiles, a wave 32 x 16 of it; ring of NBUF stages of
+// G taps of a row x 64 input channels.
+template <int TL_, int G_, int NBUF_>
+struct RwCfg {
+    static constexpr int TL = TL_, G = G_, NBUF = NBUF_, WAVES = 2 * TL / 16, THREADS = 64 * WAVES;
+    static constexpr int SPR = 6 / G;                     // stages per row of taps and k-chunk
+    static constexpr int SLICE = (RW_CO + TL) * kKStep;   // one tap, one k-chunk
+    static constexpr int STAGE = G * SLICE;
+    static constexpr int LPW = TL == 64 ? G : 5;          // copies per wave per stage
+    static_assert(TL == 64 || (TL == 32 && G == 3), "copy maps");
+    static_assert(6 % G == 0 && RW_CB * 16 * 2 == RW_CO, "stages split a row, waves the block");
+    static_assert(NBUF * STAGE + 4 * RW_CO <= (TL == 64 ? 160 : 80) * 1024, "one or two workgroups per CU");
+    static_assert((NBUF - 1) * LPW <= 63, "vmcnt range");
+    static_assert(kTilePad % TL == 0 && kCoutPad % RW_CO == 0, "blocks tile the padded sizes");
 };
-enum { RW_NONE, RW_COPY, RW_ASK };
+
+enum { RW_COPY, RW_ASK };
 
 // global -> LDS copy of 16 bytes per lane as lds_copy16, with the address as
 // a wave-uniform 64-bit base and a 32-bit lane offset.  No memory clobber: the
@@ -61,22 +68,31 @@ __device__ __forceinline__ uint32_t relu4(uint32_t w) {
     return w & ~(t | (t - (t >> 7)));
 }
 
-template <int LAYOUT, bool ONE>
-__global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
+// the same for lanes 0-31 only (512 bytes)
+__device__ __forceinline__ void lds_copy16_half(const void* base, uint32_t lane_off,
+                                                __attribute__((address_space(3))) void* dst) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b32 exec_hi, -1" ::"v"(lane_off),
+                 "s"(base), "{m0}"(m0));
+}
+
+// ONE: a single 64-channel chunk (Cin <= 64)
+template <class C, int LAYOUT, bool ONE>
+__global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
     const int8_t* __restrict__ uq, const int8_t* __restrict__ vq, const int32_t* __restrict__ bias,
     int8_t* __restrict__ y, K2Args g) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[KR_NBUF * KR_STAGE];
-    __shared__ __attribute__((aligned(16))) int bias_blk[KR_CO];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::NBUF * C::STAGE];
+    __shared__ __attribute__((aligned(16))) int bias_blk[RW_CO];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cw = wave & 1, tw = wave >> 1;
     const int lr = lane & 15, lk = lane >> 4;
-    const int nkc = g.cin_pad / kKStep;
-    const int nstage = 6 * nkc;
+    const int nkc = ONE ? 1 : g.cin_pad / kKStep;
+    const int nstage = 6 * C::SPR * nkc;
     const int lbid = xcd_remap(blockIdx.x, g.nblocks);
     const int bco = lbid % g.nbco, btl = lbid / g.nbco;
-    const int co_blk = bco * KR_CO;
-    const long long tl_blk = (long long)btl * KR_TL;
+    const int co_blk = bco * RW_CO;
+    const long long tl_blk = (long long)btl * C::TL;
     // the block's bias into LDS as the first copy of the ring, which the wait
     // for stage 0 covers (vmcnt counts in order): loaded through a register, it
     // would hold the ring's start up for a memory round trip
@@ -87,42 +103,59 @@ __global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
                      : "memory");
     }
 
-    // copy side: wave w copies row group w (16 rows; 0-3: Uq, 4-7: Vq) of each
-    // of a stage's six slices (k-blocked operands
-    // Uq[36][cin_pad/64][cout_pad][64], Vq[36][cin_pad/64][t_pad][64])
+    // copy side (k-blocked operands Uq[36][cin_pad/64][cout_pad][64],
+    // Vq[36][cin_pad/64][t_pad][64]).  A slice is 64 Uq and TL Vq rows.
+    // TL = 64: wave w copies row group w (16 rows; 0-3: Uq, 4-7: Vq) of each of a
+    // stage's slices (source u).  TL = 32 (three slices): wave w copies Uq rows
+    // 16 w .. 16 w + 15 of each (source u), and of Vq (source v) rows 16 (w % 2) ..
+    // of slice w / 2 and rows 8 w .. 8 w + 7 of slice 2.
     const int rr = lane >> 2;
     const uint32_t lane_off = (uint32_t)(rr * 64 + 16 * lds_slot(rr, lane & 3));
-    const bool copies_u = wave < 4;
-    const long long rows = copies_u ? (long long)g.cout_pad : g.t_pad;
-    const long long tap_stride = rows * g.cin_pad, kc_stride = rows * kKStep;
-    const int8_t* const src0 = copies_u ? uq + (long long)(co_blk + 16 * wave) * kKStep
-                                        : vq + (tl_blk + 16 * (wave - 4)) * kKStep;
+    const long long su = (long long)g.cout_pad * g.cin_pad, sv = g.t_pad * g.cin_pad;   // tap strides
+    const long long ku = (long long)g.cout_pad * kKStep, kv = g.t_pad * kKStep;           // k-chunk strides
+    const bool u_is_v = C::TL == 64 && wave >= 4;
+    const long long ts = u_is_v ? sv : su, ks = u_is_v ? kv : ku;
+    const int8_t* const u0 = u_is_v ? vq + (tl_blk + 16 * (wave - 4)) * kKStep
+                                    : uq + (long long)(co_blk + 16 * wave) * kKStep;
+    const int8_t* const v0 = vq + tl_blk * kKStep;
+    const long long v_full = (wave >> 1) * sv + 1024 * (wave & 1), v_half = 2 * sv + 512 * wave;
+    const int dst_u = 1024 * wave;
+    const int dst_full = (wave >> 1) * C::SLICE + RW_CO * kKStep + 1024 * (wave & 1);
+    const int dst_half = 2 * C::SLICE + RW_CO * kKStep + 512 * wave;
     constexpr uint32_t kRowOrder = 0x504321u;             // rows of taps in stream order, 4 bits each
-    const int8_t* next_src = src0 + 6 * tap_stride;
+    const int8_t* next_u = u0 + 6 * ts;
+    const int8_t* next_v = v0 + 6 * sv;
     uint32_t rows_left = kRowOrder >> 4;
-    int next_kc = 0, next_buf = 0;
-    auto issue_slice = [&](int b) __attribute__((always_inline)) {
-        lds_copy16_s(next_src + b * tap_stride, lane_off,
-                     (__attribute__((address_space(3))) void*)(lds + next_buf * KR_STAGE + 1024 * wave + b * KR_CHUNK));
+    int next_kc = 0, wr_off = 0;
+    // part i (0 .. G - 1) of the next stage's copies
+    auto issue_part = [&](int i) __attribute__((always_inline)) {
+        uint8_t* const d = lds + wr_off;
+        lds_copy16_s(next_u + i * ts, lane_off, (__attribute__((address_space(3))) void*)(d + i * C::SLICE + dst_u));
+        if (C::TL == 32 && i == 0)
+            lds_copy16_s(next_v + v_full, lane_off, (__attribute__((address_space(3))) void*)(d + dst_full));
+        if (C::TL == 32 && i == 1)
+            lds_copy16_half(next_v + v_half, lane_off, (__attribute__((address_space(3))) void*)(d + dst_half));
     };
-    auto issue_end = [&]() __attribute__((always_inline)) {
-        if (++next_kc == nkc) {
+    // step the copy side from stage j of a row of taps and k-chunk to the next
+    auto issue_end = [&](int j) __attribute__((always_inline)) {
+        if (j < C::SPR - 1) {
+            next_u += C::G * ts;
+            if (C::TL == 32) next_v += C::G * sv;
+        } else if (++next_kc == nkc) {
             next_kc = 0;
-            next_src = src0 + (long long)(6 * (int)(rows_left & 15)) * tap_stride;
+            const int a = rows_left & 15;
+            next_u = u0 + (long long)(6 * a) * ts;
+            if (C::TL == 32) next_v = v0 + (long long)(6 * a) * sv;
             rows_left >>= 4;
         } else {
-            next_src += kc_stride;
+            next_u += ks - C::G * (C::SPR - 1) * ts;
+            if (C::TL == 32) next_v += kv - C::G * (C::SPR - 1) * sv;
         }
-        next_buf = next_buf == KR_NBUF - 1 ? 0 : next_buf + 1;
-    };
-    auto issue_next = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < 6; ++b) issue_slice(b);
-        issue_end();
+        wr_off = wr_off == (C::NBUF - 1) * C::STAGE ? 0 : wr_off + C::STAGE;
     };
 
     // compute side: fragment offsets within a slice
-    const int row_a = 16 * RW_CB * cw + lr, row_b = KR_CO + 16 * tw + lr;
+    const int row_a = 16 * RW_CB * cw + lr, row_b = RW_CO + 16 * tw + lr;
     const int frag_a = row_a * 64 + 16 * lds_slot(row_a, lk);   // block c: + 16 c rows
     const int frag_b = row_b * 64 + 16 * lds_slot(row_b, lk);
     const int rnd = g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
@@ -199,83 +232,108 @@ __global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
         if (a == 5) put(3, 0, c, r, Q[k]);
     };
 
-    issue_next();
-    if (nstage > 1) issue_next();
-    int s = 0, buf = 0;
-    // One stage: six taps x 64 input channels into the row's accumulators m
-    // (from zero if FIRST).  fold_r(r), r = 0..3, folds part of the row before
-    // by VALU instructions between this stage's MFMAs: both waves of a SIMD
-    // are in the same phase, so a fold after the row's last stage would leave
-    // the matrix cores idle.
-    // COPY: whether the copies of stage s + 2 go out (RW_COPY), there is no
-    // such stage (RW_NONE), or that depends on s (RW_ASK).  Only the last row
-    // has to ask (with one 64-channel chunk, the last two have none), and
-    // without the branches a stage is one block for the scheduler.
-    auto stage = [&](auto first, auto copy, auto fold_r, v4i (&m)[6][RW_CB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < C::NBUF - 1; ++st) {             // nstage >= NBUF
+#pragma unroll
+        for (int i = 0; i < C::G; ++i) issue_part(i);
+        issue_end(st % C::SPR);
+    }
+    int s = 0, rd_off = 0;
+    // One stage: taps G j .. G j + G - 1 of a row x 64 input channels into the
+    // row's accumulators m (from zero if FIRST).  fold_b(b) folds part of the row
+    // before by VALU instructions between this stage's MFMAs: both waves of a
+    // SIMD are in the same phase, so a fold after the row's last stage would
+    // leave the matrix cores idle.
+    // COPY: the copies of stage s + NBUF - 1 go out (RW_COPY), or that depends
+    // on s (RW_ASK).  Only the last rows have to ask, and without the branches a
+    // stage is one block for the scheduler.
+    auto stage = [&](auto first, auto part, auto copy, auto fold_b, v4i (&m)[6][RW_CB])
+        __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first)::value;
-        constexpr int COPY = decltype(copy)::value;
-        // stage s has landed once only the next stage's loads are pending
-        if (COPY == RW_COPY || s + 1 < nstage)
-            WINO_WAIT_VM_LDS(RW_LPW);
-        else
-            WINO_WAIT_VM_LDS(0);
-        ring_barrier();   // stage s visible; stage s-1 (same buffer as s+2) consumed
-        // Stage s+2's copies go out one slice per tap, between the MFMAs: a
-        // copy instruction holds its wave while the load path is busy (64 B/clk
-        // per CU, 16 clk and more for each), and the six in a row kept every
-        // wave from computing for 400-700 of a stage's 1430 clk.
-        const bool more = COPY == RW_COPY || (COPY == RW_ASK && s + 2 < nstage);
-        const uint8_t* base = lds + buf * KR_STAGE;
-        buf = buf == KR_NBUF - 1 ? 0 : buf + 1;
+        constexpr int COPY = decltype(copy)::value, J = decltype(part)::value;
+        // stage s has landed once only the stages after it are pending:
+        // NBUF - 2, less at the end
+        const int later = nstage - 1 - s;
+        if (COPY == RW_COPY || later >= C::NBUF - 2) {
+            WINO_WAIT_VM_LDS((C::NBUF - 2) * C::LPW);
+        } else {
+            if (later >= 3) WINO_WAIT_VM_LDS(3 * C::LPW);
+            else if (later == 2) WINO_WAIT_VM_LDS(2 * C::LPW);
+            else if (later == 1) WINO_WAIT_VM_LDS(C::LPW);
+            else WINO_WAIT_VM_LDS(0);
+        }
+        ring_barrier();   // stage s visible; stage s - 1, whose buffer is refilled, consumed
+        // The copies go out one slice per tap, between the MFMAs: a copy
+        // instruction holds its wave while the load path is busy (64 B/clk per
+        // CU, 16 clk and more for each), and six in a row kept every wave of an
+        // earlier version from computing for 400-700 clk.
+        const bool more = COPY == RW_COPY || s + C::NBUF - 1 < nstage;
+        const uint8_t* const base = lds + rd_off;
+        rd_off = rd_off == (C::NBUF - 1) * C::STAGE ? 0 : rd_off + C::STAGE;
         ++s;
         // fragments of two taps in flight ahead of the MFMAs
         v4i fa[2][RW_CB], fb[2];
         auto frag = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < RW_CB; ++c)
-                fa[b & 1][c] = *(const v4i*)(base + b * KR_CHUNK + frag_a + 1024 * c);
-            fb[b & 1] = *(const v4i*)(base + b * KR_CHUNK + frag_b);
+                fa[b & 1][c] = *(const v4i*)(base + b * C::SLICE + frag_a + 1024 * c);
+            fb[b & 1] = *(const v4i*)(base + b * C::SLICE + frag_b);
         };
         frag(0);
         frag(1);
         const v4i zero = (v4i){0, 0, 0, 0};
 #pragma unroll
-        for (int b = 0; b < 6; ++b) {
+        for (int b = 0; b < C::G; ++b) {
+            const int t = C::G * J + b;
 #pragma unroll
             for (int c = 0; c < RW_CB; ++c)
-                m[b][c] =
-                    __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[b & 1][c], fb[b & 1], FIRST ? zero : m[b][c], 0, 0, 0);
-            if (more) issue_slice(b);
-            if (b + 2 < 6) frag(b + 2);
-            if (b > 0 && b < 5) fold_r(b - 1);
+                m[t][c] =
+                    __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[b & 1][c], fb[b & 1], FIRST ? zero : m[t][c], 0, 0, 0);
+            if (more) issue_part(b);
+            if (b + 2 < C::G) frag(b + 2);
+            fold_b(b);
             __builtin_amdgcn_sched_barrier(0);     // the taps' parts stay apart
         }
-        if (more) issue_end();
+        if (more) issue_end((J + C::NBUF - 1) % C::SPR);
     };
     const std::true_type yes;
     const std::false_type no;
-    // row of taps: accumulators m, f(c, r) folds the row before
-    auto row = [&](v4i (&m)[6][RW_CB], auto copy, auto f) __attribute__((always_inline)) {
-        if constexpr (ONE) {
-            stage(yes, copy, [&](int r) __attribute__((always_inline)) {
-                f(r >> 1, 2 * (r & 1));
-                f(r >> 1, 2 * (r & 1) + 1);
-            }, m);
-        } else {
-            stage(yes, copy, [&](int r) __attribute__((always_inline)) { f(0, r); }, m);
-            stage(no, copy, [&](int r) __attribute__((always_inline)) { f(1, r); }, m);
-            for (int kc = 2; kc < nkc; ++kc) stage(no, copy, NoFold{}, m);
+    // k-chunk 0 or 1 of a row, with its share of the row before (f(k) folds value
+    // k): two values behind taps 1-4 of a row's only chunk, else one behind taps
+    // 1-4 of the first two
+    auto chunk = [&](auto first, auto half, v4i (&m)[6][RW_CB], auto cp, auto f) __attribute__((always_inline)) {
+        constexpr int H = decltype(half)::value;
+        auto at = [&](int t) __attribute__((always_inline)) {
+            if (t < 1 || t > 4) return;
+            if (ONE) {
+                f(2 * t - 2);
+                f(2 * t - 1);
+            } else {
+                f(4 * H + t - 1);
+            }
+        };
+        stage(first, std::integral_constant<int, 0>{}, cp, [&](int b) __attribute__((always_inline)) { at(b); }, m);
+        if constexpr (C::SPR == 2)
+            stage(first, std::integral_constant<int, 1>{}, cp, [&](int b) __attribute__((always_inline)) { at(3 + b); }, m);
+    };
+    auto row = [&](v4i (&m)[6][RW_CB], auto cp, auto f) __attribute__((always_inline)) {
+        auto none = [](int) __attribute__((always_inline)) {};
+        chunk(yes, std::integral_constant<int, 0>{}, m, cp, f);
+        if constexpr (!ONE) {
+            chunk(no, std::integral_constant<int, 1>{}, m, cp, f);
+            for (int kc = 2; kc < nkc; ++kc) chunk(no, std::integral_constant<int, 1>{}, m, cp, none);
         }
     };
-    const std::integral_constant<int, RW_COPY> copy;
-    const std::integral_constant<int, ONE ? RW_NONE : RW_COPY> copy4;
-    const std::integral_constant<int, ONE ? RW_NONE : RW_ASK> copy5;
+    // with one k-chunk all of s is known at compile time; else a row has at
+    // least 2 SPR stages, and a copy reaches NBUF - 1 stages ahead
+    const std::integral_constant<int, ONE ? RW_ASK : RW_COPY> copy;
+    const std::integral_constant<int, (ONE || C::NBUF - 1 > 2 * C::SPR) ? RW_ASK : RW_COPY> copy4;
+    const std::integral_constant<int, RW_ASK> copy5;
     v4i ma[6][RW_CB], mb[6][RW_CB];
 #define RW_ROW(m, cp, mp, prev) \
-    row(m, cp, [&](int c, int r) __attribute__((always_inline)) { fold(std::integral_constant<int, prev>{}, mp, c, r); })
-    stage(yes, copy, NoFold{}, ma);
-    if constexpr (!ONE)
-        for (int kc = 1; kc < nkc; ++kc) stage(no, copy, NoFold{}, ma);
+    row(m, cp,                  \
+        [&](int k) __attribute__((always_inline)) { fold(std::integral_constant<int, prev>{}, mp, k >> 2, k & 3); })
+    row(ma, copy, [](int) __attribute__((always_inline)) {});
     RW_ROW(mb, copy, ma, 1);
     RW_ROW(ma, copy, mb, 2);
     RW_ROW(mb, copy, ma, 3);
@@ -294,7 +352,7 @@ __global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
         // gather the block's output in LDS (the ring is idle now) so that
         // every pixel's 64 channel bytes leave together
         constexpr int PITCH = 16 * 64 + 16;   // bytes per tile; the pad spreads lanes over banks
-        static_assert(KR_TL * PITCH <= KR_NBUF * KR_STAGE, "output staging fits the ring");
+        static_assert(C::TL * PITCH <= C::NBUF * C::STAGE, "output staging fits the ring");
         __syncthreads();                      // every wave is done reading the ring
         uint8_t* ot = lds + (16 * tw + lr) * PITCH + 16 * RW_CB * cw + 4 * lk;
 #pragma unroll
@@ -305,17 +363,17 @@ __global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
                 for (int j = 0; j < 4; ++j) *(uint32_t*)(ot + 64 * (4 * i + j) + 16 * c) = out[i][4 * c + j];
         __syncthreads();
         if (g.y_staged) {
-            // wave w stores tiles w, w + 8, ...: lane = 16-byte quarter q of
+            // wave w stores tiles w, w + WAVES, ...: lane = 16-byte quarter q of
             // pixel p; all LDS reads first, so that they overlap
             const int p = lane >> 2, q = lane & 3;
-            constexpr int NT = KR_TL / RW_WAVES;
+            constexpr int NT = C::TL / C::WAVES;
             v4i d[NT];
 #pragma unroll
             for (int i = 0; i < NT; ++i)
-                d[i] = *(const v4i*)(lds + (wave + RW_WAVES * i) * PITCH + 64 * p + 16 * q);
+                d[i] = *(const v4i*)(lds + (wave + C::WAVES * i) * PITCH + 64 * p + 16 * q);
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                const long long tile = tl_blk + wave + RW_WAVES * i;   // wave-uniform
+                const long long tile = tl_blk + wave + C::WAVES * i;   // wave-uniform
                 if (tile >= g.ntiles) break;
                 int img, ty, tx;
                 tile_coords(tile, g, img, ty, tx);
@@ -330,7 +388,7 @@ __global__ __launch_bounds__(RW_THREADS) void wino_tap_gemm_rows(
         } else {
             // any Cout and alignment: lane = channel, one pixel per store
             const int co = co_blk + lane;
-            for (int tl = wave; tl < KR_TL; tl += RW_WAVES) {
+            for (int tl = wave; tl < C::TL; tl += C::WAVES) {
                 const long long tile = tl_blk + tl;
                 if (tile >= g.ntiles) break;
                 int img, ty, tx;
