@@ -486,6 +486,9 @@ def main():
         nkc = (cin + 63) // 64
         nk = next(k for k in (4, 3, 2, 1) if nkc % k == 0)
         k2_name, k2_inst = "wino_tap_gemm_ws", f"wino_tap_gemm_ws<{lay}, {nk}>"
+    elif args.tap_kernel == "auto" and args.bits == 8 and info["epilogue_bits"] == 32:
+        # its block shape depends on the layer: 2,2 / 1,2 / 1,1 sixteens of channels and tiles
+        k2_name, k2_inst = "wino_tap_gemm_small", f"wino_tap_gemm_small<{mt},"
     else:
         k2_name, k2_inst = "wino_tap_gemm", f"wino_tap_gemm<{mt},{lay},{info['epilogue_bits']},0,{args.bits}>"
     k1_ms = k2_ms = None

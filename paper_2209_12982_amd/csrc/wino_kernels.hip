@@ -404,6 +404,10 @@ struct K2Args {
     int* sk_cnt;               // per split block: pieces counted (zero between launches)
     int* sk_part;              // partial Y, two slots of KR_SLOT int32 per stream-K workgroup
     FastDiv dimg, dtw;         // division by th * tw and by tw (tile coordinates)
+    // block order of wino_tap_gemm_small: nfull groups of gco channel blocks, then
+    // the rest; divisions by a full group's blocks, its channel blocks and the rest's
+    int gco, nfull;
+    FastDiv dgrp, dgco, drest;
     TapTables tab;
     uint32_t shrow[6];         // sh of row a's six taps, 5 bits each (wave-specialized kernel)
 };
@@ -1354,12 +1358,14 @@ long long resident_blocks(const wino_f4_plan_s* p, const Geometry& g) {
 
 // The tap-GEMM kernel of a convolution (a wino_tap_kernel value other than
 // AUTO and RESIDENT).  The row-streamed kernel needs the 32-bit epilogue and
-// an output convolution; AUTO takes it when its 64x64 blocks fill the device.
-// Otherwise the 64x32 tap-resident shape: on the small layers where too few
-// blocks exist the smaller shapes were measured no faster (C1-C3: 14-16 us
-// against 11-14 us), as the time there is the serial chain of ring-stage
-// latencies and the epilogue inside each block, not the block count.
-// Calibration and debug exports (MODE 1, 2) always use the 64x32 shape.
+// an output convolution; AUTO takes it from a third of the device's compute
+// units in 64x64 blocks on, below which wino_tap_gemm_small is faster (us, rows
+// against small: 144 blocks, 256 channels 19.9 / 35.2; 144 blocks, 128 channels
+// 14.0 / 24.3; 157 blocks, 64 channels 12.2 / 18.5; 64 blocks, 128 channels
+// 13.5 / 9.7; 64 blocks, 256 channels 19.5 / 13.8).  RESIDENT_64X32 under AUTO
+// stands for the kernels that keep all taps: wino_tap_gemm_small with the 32-bit
+// epilogue, else, and for calibration and debug exports (MODE 1, 2), the 64x32
+// shape.
 int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     const int k = p->tap_kernel;
     // int8/10 (fp16 operands): the row-streamed 64x32 kernel by default; a
@@ -1386,7 +1392,7 @@ int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     }
     if (p->epi_bits == 32 && k != WINO_TAP_RESIDENT &&
         (k == WINO_TAP_ROWS || k == WINO_TAP_ROWS_STREAMK ||
-         (long long)(p->cout_pad / KR_CO) * (g.t_pad / KR_TL) >= num_cus()))
+         (long long)(p->cout_pad / KR_CO) * (g.t_pad / KR_TL) * 3 >= num_cus()))
         return WINO_TAP_ROWS;
     return WINO_TAP_RESIDENT_64X32;
 }
@@ -1512,12 +1518,23 @@ wino_status launch_rows_wide(const wino_f4_plan_s* p, const Geometry& g, wino_la
 template <int M, int CB, int TB>
 wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
                          K2Args a, hipStream_t stream) {
-    a.nbco = p->cout_pad / (16 * CB);
     const int nco = (p->cout + 16 * CB - 1) / (16 * CB);   // blocks that hold channels
-    a.nbco = nco;
     const long long nb = (long long)nco * ((g.ntiles + 16 * TB - 1) / (16 * TB));
     if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
     a.nblocks = (int)nb;
+    // An XCD runs an eighth of the blocks, consecutive in this order: channel
+    // blocks in groups of gco, tile blocks along a group.  It reads the operands
+    // of about gco channel and nb / 8 / gco tile blocks into its L2, least when
+    // the two take the same bytes.
+    int gco = 1;
+    while (gco < nco && 8ll * gco * gco * CB < nb * TB) gco *= 2;
+    if (gco > nco) gco = nco;
+    const uint32_t nbt = (uint32_t)(nb / nco);
+    a.gco = gco;
+    a.nfull = nco / gco;
+    a.dgrp = make_fastdiv((uint32_t)gco * nbt);
+    a.dgco = make_fastdiv((uint32_t)gco);
+    a.drest = make_fastdiv((uint32_t)(nco % gco > 0 ? nco % gco : 1));
     if (layout == WINO_NHWC)
         hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NHWC>), dim3((unsigned)nb), dim3(64 * (M + 2)), 0,
                            stream, p->uq_dev, vq, p->bias_dev, y, a);
@@ -1526,7 +1543,24 @@ wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout
                            stream, p->uq_dev, vq, p->bias_dev, y, a);
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
-int small_shape() { static const char* e = getenv("TS"); return e ? atoi(e) : 0; }
+
+// Block shape of wino_tap_gemm_small: the largest that still gives 5/8 of the
+// compute units a block.  A block's time falls with its size only by the part
+// that is not latency, so spreading a layer further gains as long as compute
+// units are idle and loses after that, by the operand bytes (measured, us, for
+// 32x32 / 16x32 / 16x16 blocks, their counts in brackets: F4 8x32x32 128->128
+// 8.7 [64] 6.7 [128] 5.6 [256]; 256->512 13.8 [256] 18.3 [512] 21.9 [1024]; F4
+// 2x75x75 256->256 16.1 [184] 20.2 [368] 17.9 [736]; F2 8x14x14 256->256 7.8
+// [104] 6.2 [208] 6.7 [400]; F2 8x56x56 64->64 5.7 [392] 5.6 [784] 6.6 [1568]).
+template <int M>
+wino_status launch_small_auto(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
+                              int8_t* y, const K2Args& a, hipStream_t stream) {
+    const long long want = (long long)num_cus() * 5 / 8;
+    const long long t32 = (g.ntiles + 31) / 32;
+    if (t32 * ((p->cout + 31) / 32) >= want) return launch_small<M, 2, 2>(p, g, layout, vq, y, a, stream);
+    if (t32 * ((p->cout + 15) / 16) >= want) return launch_small<M, 1, 2>(p, g, layout, vq, y, a, stream);
+    return launch_small<M, 1, 1>(p, g, layout, vq, y, a, stream);
+}
 
 // ws_bytes: the workspace at vq (the stream-K split uses the part past Vq)
 template <int MODE>
@@ -1576,13 +1610,12 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
         }
         return launch_resident<K2Mid10, 4, MODE, 10>(p, g, layout, vq, y, aux, a, stream);
     }
-    if (MODE == 0 && p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO && small_shape() &&
-        (p->m == 2 || tap_kernel_for(p, g, MODE) != WINO_TAP_ROWS || small_shape() > 100)) {
-        switch (small_shape() % 100) {
-            case 11: return p->m == 2 ? launch_small<2, 1, 1>(p, g, layout, vq, y, a, stream) : launch_small<4, 1, 1>(p, g, layout, vq, y, a, stream);
-            case 12: return p->m == 2 ? launch_small<2, 1, 2>(p, g, layout, vq, y, a, stream) : launch_small<4, 1, 2>(p, g, layout, vq, y, a, stream);
-            case 21: return p->m == 2 ? launch_small<2, 2, 1>(p, g, layout, vq, y, a, stream) : launch_small<4, 2, 1>(p, g, layout, vq, y, a, stream);
-            case 22: return p->m == 2 ? launch_small<2, 2, 2>(p, g, layout, vq, y, a, stream) : launch_small<4, 2, 2>(p, g, layout, vq, y, a, stream);
+    // F2, and F4 below the row-streamed kernel's sizes, with the 32-bit epilogue
+    if constexpr (MODE == 0) {
+        if (p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO) {
+            if (p->m == 2) return launch_small_auto<2>(p, g, layout, vq, y, a, stream);
+            if (tap_kernel_for(p, g, MODE) != WINO_TAP_ROWS)
+                return launch_small_auto<4>(p, g, layout, vq, y, a, stream);
         }
     }
     if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);

@@ -16,8 +16,13 @@
 //     chunk of the row's taps is in flight per wave;
 //   * wave a then folds its row, z_a = (M'[a, :]) A (M' = M 2^sh), into LDS, and
 //     all waves apply the column pass Y = A^T z, requantize and store.
-// Every operand byte is read by 16 CB or 16 TB columns only, so large layers
-// run the LDS-staged kernels.
+// Every operand byte is read by 16 CB or 16 TB columns only, so large F4 layers
+// run the LDS-staged row-streamed kernel; F2 layers always run this one.
+// Measured against the 64 x 32 blocks it replaces (kernel time, us): F4 8x32x32
+// 128->128 16.2 -> 5.6, 256->512 22.5 -> 13.6, 2x75x75 256->256 26.0 -> 16.2; F2
+// 8x56x56 64->64 6.1 -> 5.9, 8x14x14 256->256 10.0 -> 6.4, 8x112x112 64->64 19.8
+// -> 12.4, 256x256 128->128 26.0 -> 20.8.  What is left at the small sizes is the
+// launch and two memory round trips (2.5 K clk each).
 template <int M, int CB, int TB>
 struct TsCfg {
     static constexpr int N = M + 2, CO = 16 * CB, TL = 16 * TB, THREADS = 64 * N;
@@ -38,9 +43,13 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
     const int a = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // this wave's row of taps
     const int lr = lane & 15, lk = lane >> 4;
     const int nkc = g.cin_pad / kKStep;
-    const int lbid = xcd_remap(blockIdx.x, g.nblocks);
-    const int bco = lbid % g.nbco, btl = lbid / g.nbco;
-    const int co_blk = bco * C::CO;
+    const uint32_t lbid = (uint32_t)xcd_remap(blockIdx.x, g.nblocks);
+    const uint32_t grp = min(fast_div(lbid, g.dgrp), (uint32_t)g.nfull);
+    const uint32_t rem = lbid - grp * g.dgrp.d;
+    const bool full = grp < (uint32_t)g.nfull;
+    const uint32_t btl = fast_div(rem, full ? g.dgco : g.drest);
+    const uint32_t bco = grp * g.gco + (rem - btl * (full ? g.dgco.d : g.drest.d));
+    const int co_blk = (int)bco * C::CO;
     const long long tl_blk = (long long)btl * C::TL;
 
     const uint32_t lane_off = (uint32_t)(lr * 64 + lk * 16);

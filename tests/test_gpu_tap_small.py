@@ -1,0 +1,64 @@
+"""The small-layer tap GEMM (one wave per row of taps) against the CPU oracle,
+bit for bit: each of its block shapes at ragged tile and channel counts, one
+and several 64-channel chunks, channel blocks that leave a partial group, both
+transforms and layouts."""
+import numpy as np
+import pytest
+
+import paper_2209_12982_amd as W
+import workloads
+from oracle import tapwise
+
+from gpu_util import run_conv, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+# n, cin, cout, tile rows, tile columns, cut (pixels the last tile lacks); the
+# block counts on 256 compute units select 32x32, 16x32 and 16x16 blocks
+SHAPES = [
+    (4, 70, 130, 17, 16, 1),     # 34 tile blocks of 32 x 5 channel blocks of 32
+    (3, 64, 150, 12, 16, 0),     # 18 x 10 channel blocks of 16, one chunk
+    (1, 200, 36, 5, 7, 1),       # 3 x 3 blocks of 16, four chunks
+    (1, 5, 300, 1, 3, 1),        # a single tile block, 19 channel blocks
+]
+
+
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+@pytest.mark.parametrize("m", [4, 2])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_small_tap_gemm(shape, m, layout):
+    torch_dev()
+    n, cin, cout, th, tw, cut = shape
+    h, w = m * th - cut, m * tw - cut
+    x, f, b = workloads.random_case(31, n, cin, cout, h, w, signed=True)
+    spec = tapwise.F4 if m == 4 else tapwise.F2
+    eb = tapwise.calibrate_input_exps(x, m=m)
+    relu = cut == 1
+    op = tapwise.make_plan(f, eb, bias=b, out_shift=10, relu=relu, m=m)
+    gp = (W.wino_f4_plan if m == 4 else W.wino_f2_plan)(f, eb, bias=b, out_shift=10, relu=relu)
+    assert W.wino_f4_plan_info(gp)["epilogue_bits"] == 32 and spec.m == m
+    assert W.wino_f4_tap_kernel_choice(gp, n, h, w) == W.TAP_RESIDENT_64X32
+    y = run_conv(gp, x, layout)
+    ref = tapwise.conv_int8(x, op)
+    assert (y == ref).all(), f"{(y != ref).sum()} mismatches"
+
+
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+def test_small_tap_gemm_unaligned_output(layout):
+    """An output that is not 4-byte aligned takes the byte stores."""
+    torch = torch_dev()
+    n, cin, cout, h, w = 1, 32, 64, 8, 8
+    x, f, b = workloads.random_case(32, n, cin, cout, h, w, signed=True)
+    for m, plan in ((4, W.wino_f4_plan), (2, W.wino_f2_plan)):
+        eb = tapwise.calibrate_input_exps(x, m=m)
+        gp = plan(f, eb, bias=b, out_shift=9)
+        op = tapwise.make_plan(f, eb, bias=b, out_shift=9, m=m)
+        xa = np.ascontiguousarray(x if layout == W.NCHW else x.transpose(0, 2, 3, 1))
+        buf = torch.full((n * cout * h * w + 1,), 77, dtype=torch.int8, device="cuda")
+        ws = torch.empty(W.wino_f4_workspace_bytes(gp, n, h, w), dtype=torch.int8, device="cuda")
+        W.wino_f4_conv_int8(gp, torch.from_numpy(xa).cuda(), buf[1:], n, h, w, layout, W.SPLIT, ws)
+        got = buf.cpu().numpy()
+        assert got[0] == 77
+        ref = tapwise.conv_int8(x, op)
+        ref = ref if layout == W.NCHW else ref.transpose(0, 2, 3, 1)
+        assert (got[1:] == ref.reshape(-1)).all()
