@@ -466,21 +466,23 @@ def main():
     # the tap-resident kernel's block configuration is a class argument)
     # the one-instruction requantization serves plans whose e_B are all <= 16 - bits
     k1_sat = "true" if all(0 <= e <= 16 - args.bits for e in eb) else "false"
-    if layout == W.NHWC and cin % 4 == 0:
-        # NHWC with whole 4-channel words: the transform reads global memory directly
+    if layout == W.NHWC and cin >= 4:
+        # NHWC: the transform reads global memory directly
         # tiles per block: 8 unless 16 leaves fewer idle tiles per row
         twt = (w + mt - 1) // mt
         k1_tx = 8 if (-twt) % 8 <= (-twt) % 16 else 16
         k1_name, k1_inst = "wino_input_xform_nhwc", f"wino_input_xform_nhwc<{mt},{args.bits},{k1_tx},{k1_sat}>"
     else:
-        k1_name, k1_inst = "wino_input_xform", f"wino_input_xform<{mt},{lay},0,{args.bits},16,{k1_sat}>"
+        twt = (w + mt - 1) // mt
+        k1_tx = 8 if layout == W.NCHW and (-twt) % 8 < (-twt) % 16 else 16
+        k1_name, k1_inst = "wino_input_xform", f"wino_input_xform<{mt},{lay},{args.bits},{k1_tx},{k1_sat}>"
     if rows and args.bits == 10:
         k2_name = "wino_tap_gemm_rows_wide"
         k2_inst = f"wino_tap_gemm_rows_wide<{lay},10,{'int' if info['epilogue_bits'] == 32 else 'longlong'}>"
     elif choice == W.TAP_ROWS_STREAMK:
         k2_name, k2_inst = "wino_tap_gemm_rows_sk", f"wino_tap_gemm_rows_sk<{lay}>"
     elif rows:
-        k2_name, k2_inst = "wino_tap_gemm_rows", "wino_tap_gemm_rows<RwCfg<%s>,%d,%s>" % (("32,3,4", lay, "true") if cin <= 64 else ("64,6,3", lay, "false"))
+        k2_name, k2_inst = "wino_tap_gemm_rows", "wino_tap_gemm_rows<RwCfg<%s>,%d,%s>" % (("32,3,4", lay, "true,0") if cin <= 64 else ("64,6,3", lay, "false,0"))
     elif choice == W.TAP_WAVES:
         # 64-channel chunks per ring stage: the largest of 4, 3, 2, 1 dividing the padded chunks
         nkc = (cin + 63) // 64

@@ -141,9 +141,10 @@ wino_status wino_f4_plan_tables(const float* w_oihw, int32_t cin, int32_t cout, 
 /*
  * wino_f4_plan_set_tap_kernel -- choose the tap-GEMM kernel (wino_tap_kernel)
  * for later SPLIT convolutions with this plan.  ROWS applies to output
- * convolutions with the 32-bit epilogue (else the RESIDENT choice is made);
- * calibration and debug exports always use the 64 x 32 RESIDENT shape.  Not
- * to be called while a convolution with the plan is being enqueued on
+ * convolutions with the 32-bit epilogue (else the RESIDENT choice is made).
+ * Output calibration runs the convolution's kernels under AUTO and the 64 x 32
+ * RESIDENT shape under a forced choice; debug exports always use the latter.
+ * Not to be called while a convolution with the plan is being enqueued on
  * another thread.
  * Errors: WINO_EINVAL (null plan, unknown kind).
  */

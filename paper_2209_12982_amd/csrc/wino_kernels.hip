@@ -52,7 +52,7 @@ struct K1Args {
     int n, cin, h, w, th, tw, cin_pad;
     int ntxb, ncg;
     int x_vec;                          // 16-byte loads allowed (Cin % 16 == 0, x aligned)
-    int x_dw;                           // NCHW word loads allowed (W % 4 == 0, x aligned, image < 2 GiB)
+    int x_dw;                           // NCHW word loads allowed (W >= 4, image < 2 GiB)
     int vq_buf;                         // tap planes below 4 GiB: buffer stores with a scalar base
     long long t_pad;                    // tile stride of a tap plane in Vq
     long long plane_bytes;              // bytes of one tap plane of Vq
@@ -141,15 +141,16 @@ __device__ __forceinline__ void k1_stage_band(uint32_t* lds, const int8_t* __res
             *(uint4*)(lds + pix * K1_CS + 4 * part) = v;
         }
     } else if (g.x_dw) {
-        // NCHW with W % 4 == 0: an item moves 4 channels x 8 band columns of
-        // one band row.  The band starts at column M tx0 - 1, so a group of
-        // eight columns straddles three aligned words of each channel's image
-        // row: three word loads and two byte alignments per channel, then two
-        // 4x4 byte transposes (the four channels of a column into one word)
-        // and eight LDS word stores.  A word left or right of the image row,
-        // in a row outside the image or of a channel >= Cin gets an offset
-        // past the image's bytes and reads as zero (with W % 4 == 0 a word is
-        // either wholly inside a row or wholly outside it).
+        // NCHW, W >= 4: an item moves 4 channels x 8 band columns of one band row:
+        // two word loads per channel at any byte address (the band starts at
+        // column M tx0 - 1 and rows of odd width at any byte), then two 4x4 byte
+        // transposes (the four channels of a column into one word) and eight LDS
+        // word stores.  A word that sticks out left or right of the image row is
+        // read from inside the row and shifted, which puts zeros outside; a word
+        // wholly outside, in a row outside the image or of a channel >= Cin gets
+        // an offset past the image's bytes and reads as zero.  (2x256x75x75: 8.3
+        // us against 33 with a byte gather; W % 4 == 0, 1x64x568x568: 17.9 against
+        // 18.9 with three aligned words per channel.)
         constexpr int NG = (COLS + 7) / 8;
         constexpr int kOut = 0x7ffffff0;  // >= the image's bytes (checked on the host)
         const int img_bytes = g.cin * g.h * g.w;
@@ -160,25 +161,26 @@ __device__ __forceinline__ void k1_stage_band(uint32_t* lds, const int8_t* __res
             const int rest = id / NG;
             const int r = rest % ROWS, cq = rest / ROWS;
             const int hh = h0 + r;
-            const int cc = w0 + 8 * gc;           // first column of the group
-            const int a = cc >> 2;                // its word (floor), then the next two
-            const int sh = cc & 3;                // byte offset of the group in word a
             const bool rok = hh >= 0 && hh < g.h;
-            const bool ok0 = rok && a >= 0 && 4 * a < g.w;
-            const bool ok1 = rok && a + 1 >= 0 && 4 * (a + 1) < g.w;
-            const bool ok2 = rok && a + 2 >= 0 && 4 * (a + 2) < g.w;
-            const int hr = rok ? hh : 0;
+            int col[2], left[2], right[2];        // column read, shifts in bits
+            bool ok[2];
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const int c4 = w0 + 8 * gc + 4 * hf;       // >= -1
+                ok[hf] = rok && c4 < g.w;
+                col[hf] = max(0, min(c4, g.w - 4));
+                left[hf] = 8 * max(col[hf] - c4, 0);
+                right[hf] = 8 * max(c4 - col[hf], 0) & 31;
+            }
             uint32_t v[2][4];
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
                 const int ci = ci0 + 4 * cq + kk;
-                const bool cok = ci < g.cin;
-                const int base = ((cok ? ci : 0) * g.h + hr) * g.w + 4 * a;
-                const uint32_t w0_ = __builtin_amdgcn_raw_buffer_load_b32(rs, cok && ok0 ? base : kOut, 0, 0);
-                const uint32_t w1_ = __builtin_amdgcn_raw_buffer_load_b32(rs, cok && ok1 ? base + 4 : kOut, 0, 0);
-                const uint32_t w2_ = __builtin_amdgcn_raw_buffer_load_b32(rs, cok && ok2 ? base + 8 : kOut, 0, 0);
-                v[0][kk] = __builtin_amdgcn_alignbyte(w1_, w0_, (uint32_t)sh);
-                v[1][kk] = __builtin_amdgcn_alignbyte(w2_, w1_, (uint32_t)sh);
+                const int row = (ci * g.h + hh) * g.w;
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf)
+                    v[hf][kk] = __builtin_amdgcn_raw_buffer_load_b32(rs, ok[hf] && ci < g.cin ? row + col[hf] : kOut, 0, 0)
+                                    >> right[hf] << left[hf];
             }
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
@@ -187,14 +189,14 @@ __device__ __forceinline__ void k1_stage_band(uint32_t* lds, const int8_t* __res
                 const uint32_t ab_hi = __builtin_amdgcn_perm(v[hf][1], v[hf][0], 0x07030602u);
                 const uint32_t cd_lo = __builtin_amdgcn_perm(v[hf][3], v[hf][2], 0x05010400u);
                 const uint32_t cd_hi = __builtin_amdgcn_perm(v[hf][3], v[hf][2], 0x07030602u);
-                const uint32_t col[4] = {__builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u),
-                                         __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u),
-                                         __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u),
-                                         __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u)};
+                const uint32_t quad[4] = {__builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u),
+                                          __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u),
+                                          __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u),
+                                          __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u)};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int c = 8 * gc + 4 * hf + j;
-                    if (c < COLS) lds[(r * COLS + c) * K1_CS + cq] = col[j];
+                    if (c < COLS) lds[(r * COLS + c) * K1_CS + cq] = quad[j];
                 }
             }
         }
@@ -213,25 +215,23 @@ __device__ __forceinline__ void k1_stage_band(uint32_t* lds, const int8_t* __res
     }
 }
 
-// MODE 0: write Vq.  MODE 1: per-tap max |V| into tapmax[NTAP] (calibration).
+// Writes Vq.
 // Q: Winograd-domain width, 8 (int8 Vq) or 10 (int8/10: fp16 Vq holding
 // 10-bit integers, [ntap][cin_pad/32][t_pad][32]).
 // SAT: requantize with the one-instruction saturating form (every e_B <=
 // 16 - Q), a kernel of its own so the other form's per-tap constants are not
 // held in scalar registers too.
-template <int M, int LAYOUT, int MODE, int Q = 8, int TX = K1_TX, bool SAT = false>
+template <int M, int LAYOUT, int Q = 8, int TX = K1_TX, bool SAT = false>
 __global__ __launch_bounds__(16 * TX, 5) void wino_input_xform(const int8_t* __restrict__ x,
-                                                               int8_t* __restrict__ vq,
-                                                               int* __restrict__ tapmax, K1Args g) {
-    constexpr int N = Wino<M>::N, NT = Wino<M>::NTAP;
+                                                               int8_t* __restrict__ vq, K1Args g) {
+    constexpr int N = Wino<M>::N;
     constexpr int COLS = K1Band<M, TX>::COLS;
     __shared__ uint32_t band[K1Band<M, TX>::ROWS * COLS * K1_CS];
-    __shared__ int red[NT];
     // Logical block order: channel group fastest, then tile-column block,
     // then tile row; consecutive logical ids are kept on one XCD (its L2),
     // so the channel groups sharing each 128-byte line of an NHWC pixel and
     // the tile rows sharing halo rows are read by concurrent workgroups.
-    if constexpr (MODE == 0) k1_zero_counters(g);
+    k1_zero_counters(g);
     int bid = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int cgi = bid % g.ncg;
     bid /= g.ncg;
@@ -239,7 +239,6 @@ __global__ __launch_bounds__(16 * TX, 5) void wino_input_xform(const int8_t* __r
     const int row = bid / g.ntxb;         // img * th + ty
     const int img = row / g.th, ty = row - img * g.th;
     const int tx0 = txb * TX, ci0 = cgi * K1_CG;
-    if (MODE == 1 && threadIdx.x < NT) red[threadIdx.x] = 0;
 
     k1_stage_band<M, LAYOUT, TX>(band, x, g, img, ty, tx0, ci0);
     __syncthreads();
@@ -258,31 +257,16 @@ __global__ __launch_bounds__(16 * TX, 5) void wino_input_xform(const int8_t* __r
     v2s ev[N][N], od[N][N];
     input_tile_transform<M>(wv, ev, od);
 
-    if (MODE == 0) {
-        if (!valid) return;
-        const long long tile = (long long)row * g.tw + tx;
-        // byte offset of this thread's values within a tap plane:
-        //   Q = 8:  Vq[t][cgi][tile][64], 4 bytes (channels 4q .. 4q + 3)
-        //   Q = 10: Vq[t][2 cgi + q / 8][tile][32] fp16 (this block's 64
-        //           channels are the 32-channel k rows 2 cgi and 2 cgi + 1),
-        //           8 bytes (4 halves)
-        const long long off = Q == 10 ? (((long long)(2 * cgi + (q >> 3)) * g.t_pad + tile) * 32 + 4 * (q & 7)) * 2
-                                      : ((long long)cgi * g.t_pad + tile) * K1_CG + 4 * q;
-        k1_store<N, Q, SAT>(ev, od, g, vq, off);
-    } else {
-        if (valid) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                v2s a = ev[t / N][t % N], b = od[t / N][t % N];
-                a = __builtin_elementwise_max(a, -a);
-                b = __builtin_elementwise_max(b, -b);
-                int m = max(max((int)a.x, (int)a.y), max((int)b.x, (int)b.y));
-                atomicMax(&red[t], m);
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < NT) atomicMax(&tapmax[threadIdx.x], red[threadIdx.x]);
-    }
+    if (!valid) return;
+    const long long tile = (long long)row * g.tw + tx;
+    // byte offset of this thread's values within a tap plane:
+    //   Q = 8:  Vq[t][cgi][tile][64], 4 bytes (channels 4q .. 4q + 3)
+    //   Q = 10: Vq[t][2 cgi + q / 8][tile][32] fp16 (this block's 64
+    //           channels are the 32-channel k rows 2 cgi and 2 cgi + 1),
+    //           8 bytes (4 halves)
+    const long long off = Q == 10 ? (((long long)(2 * cgi + (q >> 3)) * g.t_pad + tile) * 32 + 4 * (q & 7)) * 2
+                                  : ((long long)cgi * g.t_pad + tile) * K1_CG + 4 * q;
+    k1_store<N, Q, SAT>(ev, od, g, vq, off);
 }
 
 // K1 for NHWC input without the LDS band: each thread reads its tile's
@@ -293,11 +277,43 @@ __global__ __launch_bounds__(16 * TX, 5) void wino_input_xform(const int8_t* __r
 // the row's end left or right of the image, for idle tiles and for channels
 // >= Cin), so pixels outside the image read as zero with no arithmetic per
 // load.  No LDS and no barrier: one wave's loads overlap other waves'
-// arithmetic.  Needs Cin % 4 == 0 (whole 4-channel words), a 4-byte aligned
-// x and image rows below 2 GiB.
+// arithmetic.  Needs Cin >= 4, a 4-byte aligned x and image rows below 2 GiB.
+// With Cin % 4 != 0 the words lie at any byte address, and a thread of the last
+// 1-3 channels reads the word that ends with them and shifts it down.
 // TX = 16 or 8 tiles per block (256 or 128 threads), 20 waves per CU either
 // way; the launch takes the width that leaves fewer idle tiles at the end of
 // a tile row (C5's rows of 40 tiles: 8, measured 16.6 -> 15.0 us).
+template <int M, int N = Wino<M>::N>
+__device__ __forceinline__ void k1_load_nhwc(uint32_t (&wv)[N][N], const int8_t* __restrict__ x, const K1Args& g, int img,
+                                             int ty, int tx, int ci) {
+    const bool lane_ok = tx < g.tw && ci < g.cin;
+    const int cread = min(ci, g.cin - 4);
+    const int row_bytes = g.w * g.cin;
+    constexpr int kOut = 0x7ffffff0;      // >= any row's num_records
+    int coff[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        const int xx = M * tx - 1 + c;
+        coff[c] = (lane_ok && xx >= 0 && xx < g.w) ? xx * g.cin + cread : kOut;
+    }
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        const int yy = M * ty - 1 + r;
+        const bool rok = yy >= 0 && yy < g.h;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(x + (rok ? ((long long)img * g.h + yy) * row_bytes : 0)), 0, rok ? row_bytes : 0, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < N; ++c) wv[r][c] = __builtin_amdgcn_raw_buffer_load_b32(rs, coff[c], 0, 0);
+    }
+    if (g.cin & 3) {
+        const int sh = 8 * (ci - cread) & 31;       // 0 for whole words; lanes past Cin hold zeros
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int c = 0; c < N; ++c) wv[r][c] >>= sh;
+    }
+}
+
 template <int M, int Q, int TX, bool SAT>
 __global__ __launch_bounds__(16 * TX, 80 / TX) void wino_input_xform_nhwc(const int8_t* __restrict__ x,
                                                                     int8_t* __restrict__ vq, K1Args g) {
@@ -312,26 +328,8 @@ __global__ __launch_bounds__(16 * TX, 80 / TX) void wino_input_xform_nhwc(const 
     const int img = row / g.th, ty = row - img * g.th;
     const int q = threadIdx.x & 15, j = threadIdx.x >> 4;
     const int tx = txb * TX + j;
-    const int ci = cgi * K1_CG + 4 * q;
-    const bool lane_ok = tx < g.tw && ci < g.cin;
-    const int row_bytes = g.w * g.cin;
-    constexpr int kOut = 0x7ffffff0;      // >= any row's num_records
-    int coff[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-        const int xx = M * tx - 1 + c;
-        coff[c] = (lane_ok && xx >= 0 && xx < g.w) ? xx * g.cin + ci : kOut;
-    }
     uint32_t wv[N][N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        const int yy = M * ty - 1 + r;
-        const bool rok = yy >= 0 && yy < g.h;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(x + (rok ? ((long long)img * g.h + yy) * row_bytes : 0)), 0, rok ? row_bytes : 0, 0x00020000);
-#pragma unroll
-        for (int c = 0; c < N; ++c) wv[r][c] = __builtin_amdgcn_raw_buffer_load_b32(rs, coff[c], 0, 0);
-    }
+    k1_load_nhwc<M>(wv, x, g, img, ty, tx, cgi * K1_CG + 4 * q);
     v2s ev[N][N], od[N][N];
     input_tile_transform<M>(wv, ev, od);
     if (tx >= g.tw) return;
@@ -339,6 +337,92 @@ __global__ __launch_bounds__(16 * TX, 80 / TX) void wino_input_xform_nhwc(const 
     const long long off = Q == 10 ? (((long long)(2 * cgi + (q >> 3)) * g.t_pad + tile) * 32 + 4 * (q & 7)) * 2
                                   : ((long long)cgi * g.t_pad + tile) * K1_CG + 4 * q;
     k1_store<N, Q, SAT>(ev, od, g, vq, off);
+}
+
+// Calibration: per-tap max |V|, the transform of K1 without its stores.  Each
+// workgroup walks the blocks b, b + G, ... of a grid of G, keeps the running
+// maxima of its threads in packed 16-bit lanes (|V| <= 12768) and writes one
+// partial per tap to part[block][NTAP]; wino_absmax_reduce takes the maximum over
+// the workgroups.  (One LDS atomic per value and tap and one global atomic per
+// workgroup and tap took 121 us on 1x128x256x512; 18.5 us this way.)
+constexpr int kNhwcBand = 2;
+template <int M, int LAYOUT, int TX>
+__global__ __launch_bounds__(16 * TX) void wino_input_absmax(const int8_t* __restrict__ x, int* __restrict__ part,
+                                                             int nblocks, K1Args g) {
+    constexpr int N = Wino<M>::N, NT = Wino<M>::NTAP, COLS = K1Band<M, TX>::COLS, WAVES = 16 * TX / 64;
+    constexpr bool DIRECT = LAYOUT == WINO_NHWC;    // kNhwcBand: NHWC through the band
+    constexpr int BAND = LAYOUT == kNhwcBand ? (int)WINO_NHWC : LAYOUT;
+    __shared__ uint32_t band[DIRECT ? 1 : K1Band<M, TX>::ROWS * COLS * K1_CS];
+    __shared__ int red[WAVES][NT];
+    const int q = threadIdx.x & 15, j = threadIdx.x >> 4;
+    v2s mx[N][N];
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+#pragma unroll
+        for (int c = 0; c < N; ++c) mx[r][c] = splat(0);
+    for (int lb = blockIdx.x; lb < nblocks; lb += gridDim.x) {
+        const int cgi = lb % g.ncg, rest = lb / g.ncg;
+        const int txb = rest % g.ntxb, row = rest / g.ntxb;
+        const int img = row / g.th, ty = row - img * g.th;
+        const int tx = txb * TX + j;
+        uint32_t wv[N][N];
+        if constexpr (DIRECT) {
+            k1_load_nhwc<M>(wv, x, g, img, ty, tx, cgi * K1_CG + 4 * q);
+        } else {
+            __syncthreads();               // the band's last readers are done
+            k1_stage_band<M, BAND, TX>(band, x, g, img, ty, txb * TX, cgi * K1_CG);
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+#pragma unroll
+                for (int c = 0; c < N; ++c) wv[r][c] = tx < g.tw ? band[(r * COLS + M * j + c) * K1_CS + q] : 0u;
+        }
+        v2s ev[N][N], od[N][N];
+        input_tile_transform<M>(wv, ev, od);
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int c = 0; c < N; ++c)
+                mx[r][c] = __builtin_elementwise_max(
+                    mx[r][c], __builtin_elementwise_max(__builtin_elementwise_max(ev[r][c], -ev[r][c]),
+                                                        __builtin_elementwise_max(od[r][c], -od[r][c])));
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        int v = max((int)mx[t / N][t % N].x, (int)mx[t / N][t % N].y);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+        if (lane == 0) red[wave][t] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < NT) {
+        int v = red[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v = max(v, red[w][threadIdx.x]);
+        part[(size_t)blockIdx.x * NT + threadIdx.x] = v;
+    }
+}
+
+// out[t] = max over the kAbsmaxGroups or fewer workgroups of part[.][t]: one
+// workgroup per tap, so that each thread has its few loads in flight together
+// (one workgroup for all taps: 17.7 us, a chain of loads)
+constexpr int kAbsmaxGroups = 1024;
+__global__ __launch_bounds__(256) void wino_absmax_reduce(const int* __restrict__ part, int n, int ntap,
+                                                          int* __restrict__ out) {
+    __shared__ int red[4];
+    const int t = blockIdx.x;
+    int v = 0;
+#pragma unroll
+    for (int i = 0; i < kAbsmaxGroups / 256; ++i) {
+        const int b = (int)threadIdx.x + 256 * i;
+        v = max(v, b < n ? part[(size_t)b * ntap + t] : 0);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) out[t] = max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
 // ---------------------------------------------------------------------------
@@ -1304,51 +1388,92 @@ int k1_direct_tx(int tw) {
     return idle8 <= idle16 ? 8 : 16;
 }
 
-template <int M, int MODE, int Q, int TX>
-wino_status launch_k1_tx(const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq, int* tapmax,
-                         hipStream_t stream) {
+// whether the direct NHWC kernel takes this input
+bool k1_direct(const K1Args& a, wino_layout layout, const int8_t* x) {
+    return layout == WINO_NHWC && a.cin >= 4 && ((uintptr_t)x & 3) == 0 && (long long)a.w * a.cin < 0x7ffffff0ll;
+}
+
+// the arguments' block geometry for TX tiles per block, and the blocks
+template <int TX>
+K1Args k1_blocks(const K1Args& a, wino_layout layout, const int8_t* x, long long& blocks) {
     K1Args args = a;
     args.ntxb = (a.tw + TX - 1) / TX;
-    long long blocks = (long long)args.ntxb * a.ncg * a.n * a.th;
-    if (blocks == 0) return WINO_OK;
-    if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
     args.x_vec = (a.cin % 16 == 0) && (((uintptr_t)x & 15) == 0);
-    args.x_dw = layout == WINO_NCHW && a.w % 4 == 0 && (((uintptr_t)x & 3) == 0) &&
-                (long long)a.cin * a.h * a.w < 0x7ffffff0ll;
-#define K1_LAUNCH(L, S)                                                                                      \
-    hipLaunchKernelGGL((wino_input_xform<M, L, MODE, Q, TX, S>), dim3((unsigned)blocks), dim3(16 * TX), 0, stream, \
-                       x, vq, tapmax, args)
-    const bool sat = MODE == 0 && a.q_sat;
-    if constexpr (MODE == 0) {
-        if (layout == WINO_NHWC && a.cin % 4 == 0 && ((uintptr_t)x & 3) == 0 && (long long)a.w * a.cin < 0x7ffffff0ll) {
-            const int tx = k1_direct_tx(a.tw);
-            args.ntxb = (a.tw + tx - 1) / tx;
-            const long long nb = (long long)args.ntxb * a.ncg * a.n * a.th;
-            if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
-#define K1D_LAUNCH(T, S)                                                                                            \
-    hipLaunchKernelGGL((wino_input_xform_nhwc<M, Q, T, S>), dim3((unsigned)nb), dim3(16 * T), 0, stream, x, vq, args)
-            if (tx == 8) {
-                if (sat) K1D_LAUNCH(8, true); else K1D_LAUNCH(8, false);
-            } else {
-                if (sat) K1D_LAUNCH(16, true); else K1D_LAUNCH(16, false);
-            }
-#undef K1D_LAUNCH
-            return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
-        }
-    }
-    if (layout == WINO_NHWC) {
-        if (sat) K1_LAUNCH(WINO_NHWC, MODE == 0); else K1_LAUNCH(WINO_NHWC, false);
-    } else {
-        if (sat) K1_LAUNCH(WINO_NCHW, MODE == 0); else K1_LAUNCH(WINO_NCHW, false);
-    }
-#undef K1_LAUNCH
+    args.x_dw = layout == WINO_NCHW && a.w >= 4 && (long long)a.cin * a.h * a.w < 0x7ffffff0ll;
+    blocks = (long long)args.ntxb * a.ncg * a.n * a.th;
+    return args;
+}
+
+template <int M, int Q, int TX>
+wino_status launch_k1_direct(const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq, hipStream_t stream) {
+    long long blocks;
+    const K1Args args = k1_blocks<TX>(a, layout, x, blocks);
+    if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
+    if (a.q_sat)
+        hipLaunchKernelGGL((wino_input_xform_nhwc<M, Q, TX, true>), dim3((unsigned)blocks), dim3(16 * TX), 0, stream, x,
+                           vq, args);
+    else
+        hipLaunchKernelGGL((wino_input_xform_nhwc<M, Q, TX, false>), dim3((unsigned)blocks), dim3(16 * TX), 0, stream, x,
+                           vq, args);
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
-template <int M, int MODE, int Q = 8>
-wino_status launch_k1(const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq, int* tapmax,
-                      hipStream_t stream) {
-    return launch_k1_tx<M, MODE, Q, K1_TX>(a, layout, x, vq, tapmax, stream);
+template <int M, int LAYOUT, int Q, int TX>
+wino_status launch_k1_band(const K1Args& a, const int8_t* x, int8_t* vq, hipStream_t stream) {
+    long long blocks;
+    const K1Args args = k1_blocks<TX>(a, (wino_layout)LAYOUT, x, blocks);
+    if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
+    if (a.q_sat)
+        hipLaunchKernelGGL((wino_input_xform<M, LAYOUT, Q, TX, true>), dim3((unsigned)blocks), dim3(16 * TX), 0, stream,
+                           x, vq, args);
+    else
+        hipLaunchKernelGGL((wino_input_xform<M, LAYOUT, Q, TX, false>), dim3((unsigned)blocks), dim3(16 * TX), 0, stream,
+                           x, vq, args);
+    return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+}
+
+template <int M, int Q>
+wino_status launch_k1(const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq, hipStream_t stream) {
+    if (k1_direct(a, layout, x))
+        return k1_direct_tx(a.tw) == 8 ? launch_k1_direct<M, Q, 8>(a, layout, x, vq, stream)
+                                       : launch_k1_direct<M, Q, 16>(a, layout, x, vq, stream);
+    if (layout == WINO_NHWC) return launch_k1_band<M, WINO_NHWC, Q, K1_TX>(a, x, vq, stream);
+    // NCHW: 8 tiles per block where that leaves fewer idle tiles in a row; on a
+    // tie 16, whose band has the smaller share of halo columns (1x64x568x568, rows
+    // of 142 tiles: 17.9 us against 20.8)
+    if ((a.tw + 7) / 8 * 8 < (a.tw + 15) / 16 * 16) return launch_k1_band<M, WINO_NCHW, Q, 8>(a, x, vq, stream);
+    return launch_k1_band<M, WINO_NCHW, Q, K1_TX>(a, x, vq, stream);
+}
+
+// Per-tap maxima of |V| over the input into out[ntap]; scratch: kAbsmaxGroups x
+// ntap int32.  Inputs that the direct kernel does not take go through the band.
+template <int M>
+wino_status launch_absmax(const K1Args& a, wino_layout layout, const int8_t* x, int* out, int* scratch,
+                          hipStream_t stream) {
+    constexpr int NT = Wino<M>::NTAP;
+    long long blocks;
+    K1Args args;
+    int groups;
+    if (k1_direct(a, layout, x)) {
+        args = k1_blocks<8>(a, layout, x, blocks);
+        if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
+        groups = (int)std::min<long long>(blocks, kAbsmaxGroups);
+        hipLaunchKernelGGL((wino_input_absmax<M, WINO_NHWC, 8>), dim3(groups), dim3(128), 0, stream, x, scratch,
+                           (int)blocks, args);
+    } else {
+        args = k1_blocks<K1_TX>(a, layout, x, blocks);
+        if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
+        groups = (int)std::min<long long>(blocks, kAbsmaxGroups);
+        if (layout == WINO_NCHW)
+            hipLaunchKernelGGL((wino_input_absmax<M, WINO_NCHW, K1_TX>), dim3(groups), dim3(16 * K1_TX), 0, stream, x,
+                               scratch, (int)blocks, args);
+        else
+            hipLaunchKernelGGL((wino_input_absmax<M, kNhwcBand, K1_TX>), dim3(groups), dim3(16 * K1_TX), 0, stream, x,
+                               scratch, (int)blocks, args);
+    }
+    if (hipGetLastError() != hipSuccess) return WINO_EHIP;
+    hipLaunchKernelGGL(wino_absmax_reduce, dim3(NT), dim3(256), 0, stream, scratch, groups, NT, out);
+    return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
 template <class C>
@@ -1364,8 +1489,8 @@ long long resident_blocks(const wino_f4_plan_s* p, const Geometry& g) {
 // 14.0 / 24.3; 157 blocks, 64 channels 12.2 / 18.5; 64 blocks, 128 channels
 // 13.5 / 9.7; 64 blocks, 256 channels 19.5 / 13.8).  RESIDENT_64X32 under AUTO
 // stands for the kernels that keep all taps: wino_tap_gemm_small with the 32-bit
-// epilogue, else, and for calibration and debug exports (MODE 1, 2), the 64x32
-// shape.
+// epilogue, else the 64x32 shape.  Debug exports (MODE 2), and calibration
+// (MODE 1) of a plan with a forced kernel, use the 64x32 shape.
 int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     const int k = p->tap_kernel;
     // int8/10 (fp16 operands): the row-streamed 64x32 kernel by default; a
@@ -1408,19 +1533,28 @@ int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
 using RwNarrow = RwCfg<32, 3, 4>;
 using RwWide = RwCfg<64, 6, 3>;
 
-template <class C, bool ONE>
+template <class C, bool ONE, int MODE>
 wino_status launch_rows(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
-                        K2Args a, hipStream_t stream) {
+                        void* aux, K2Args a, hipStream_t stream) {
     const long long nb = (long long)(p->cout_pad / RW_CO) * ((g.ntiles + C::TL - 1) / C::TL);
     if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
+    a.nbco = p->cout_pad / RW_CO;
     a.nblocks = (int)nb;
-    if (layout == WINO_NHWC)
-        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NHWC, ONE>), dim3((unsigned)nb), dim3(C::THREADS), 0, stream,
-                           p->uq_dev, vq, p->bias_dev, y, a);
+    const dim3 grid((unsigned)nb), block(C::THREADS);
+    if (MODE == 1 || layout == WINO_NHWC)                  // the maximum takes no layout
+        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NHWC, ONE, MODE>), grid, block, 0, stream, p->uq_dev, vq,
+                           p->bias_dev, y, aux, a);
     else
-        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NCHW, ONE>), dim3((unsigned)nb), dim3(C::THREADS), 0, stream,
-                           p->uq_dev, vq, p->bias_dev, y, a);
+        hipLaunchKernelGGL((wino_tap_gemm_rows<C, WINO_NCHW, ONE, 0>), grid, block, 0, stream, p->uq_dev, vq,
+                           p->bias_dev, y, aux, a);
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+}
+
+template <int MODE>
+wino_status launch_rows_auto(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
+                             void* aux, const K2Args& a, hipStream_t stream) {
+    return p->cin_pad == kKStep ? launch_rows<RwNarrow, true, MODE>(p, g, layout, vq, y, aux, a, stream)
+                                : launch_rows<RwWide, false, MODE>(p, g, layout, vq, y, aux, a, stream);
 }
 
 // 64-channel chunks per ring stage of the wave-specialized kernel: the
@@ -1515,9 +1649,9 @@ wino_status launch_rows_wide(const wino_f4_plan_s* p, const Geometry& g, wino_la
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
-template <int M, int CB, int TB>
+template <int M, int CB, int TB, int MODE>
 wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq, int8_t* y,
-                         K2Args a, hipStream_t stream) {
+                         void* aux, K2Args a, hipStream_t stream) {
     const int nco = (p->cout + 16 * CB - 1) / (16 * CB);   // blocks that hold channels
     const long long nb = (long long)nco * ((g.ntiles + 16 * TB - 1) / (16 * TB));
     if (nb > 0x7fffffffll) return WINO_EUNSUPPORTED;
@@ -1535,12 +1669,13 @@ wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout
     a.dgrp = make_fastdiv((uint32_t)gco * nbt);
     a.dgco = make_fastdiv((uint32_t)gco);
     a.drest = make_fastdiv((uint32_t)(nco % gco > 0 ? nco % gco : 1));
-    if (layout == WINO_NHWC)
-        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NHWC>), dim3((unsigned)nb), dim3(64 * (M + 2)), 0,
-                           stream, p->uq_dev, vq, p->bias_dev, y, a);
+    const dim3 grid((unsigned)nb), block(64 * (M + 2));
+    if (MODE == 1 || layout == WINO_NHWC)                  // the maximum takes no layout
+        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NHWC, MODE>), grid, block, 0, stream, p->uq_dev, vq,
+                           p->bias_dev, y, aux, a);
     else
-        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NCHW>), dim3((unsigned)nb), dim3(64 * (M + 2)), 0,
-                           stream, p->uq_dev, vq, p->bias_dev, y, a);
+        hipLaunchKernelGGL((wino_tap_gemm_small<M, CB, TB, WINO_NCHW, 0>), grid, block, 0, stream, p->uq_dev, vq,
+                           p->bias_dev, y, aux, a);
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
@@ -1552,14 +1687,14 @@ wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout
 // 8.7 [64] 6.7 [128] 5.6 [256]; 256->512 13.8 [256] 18.3 [512] 21.9 [1024]; F4
 // 2x75x75 256->256 16.1 [184] 20.2 [368] 17.9 [736]; F2 8x14x14 256->256 7.8
 // [104] 6.2 [208] 6.7 [400]; F2 8x56x56 64->64 5.7 [392] 5.6 [784] 6.6 [1568]).
-template <int M>
+template <int M, int MODE>
 wino_status launch_small_auto(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
-                              int8_t* y, const K2Args& a, hipStream_t stream) {
+                              int8_t* y, void* aux, const K2Args& a, hipStream_t stream) {
     const long long want = (long long)num_cus() * 5 / 8;
     const long long t32 = (g.ntiles + 31) / 32;
-    if (t32 * ((p->cout + 31) / 32) >= want) return launch_small<M, 2, 2>(p, g, layout, vq, y, a, stream);
-    if (t32 * ((p->cout + 15) / 16) >= want) return launch_small<M, 1, 2>(p, g, layout, vq, y, a, stream);
-    return launch_small<M, 1, 1>(p, g, layout, vq, y, a, stream);
+    if (t32 * ((p->cout + 31) / 32) >= want) return launch_small<M, 2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
+    if (t32 * ((p->cout + 15) / 16) >= want) return launch_small<M, 1, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
+    return launch_small<M, 1, 1, MODE>(p, g, layout, vq, y, aux, a, stream);
 }
 
 // ws_bytes: the workspace at vq (the stream-K split uses the part past Vq)
@@ -1610,12 +1745,14 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
         }
         return launch_resident<K2Mid10, 4, MODE, 10>(p, g, layout, vq, y, aux, a, stream);
     }
-    // F2, and F4 below the row-streamed kernel's sizes, with the 32-bit epilogue
-    if constexpr (MODE == 0) {
+    // AUTO with the 32-bit epilogue, a convolution or its output maximum: F4 from
+    // the row-streamed kernel's sizes on, and the small-layer kernel
+    if constexpr (MODE <= 1) {
         if (p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO) {
-            if (p->m == 2) return launch_small_auto<2>(p, g, layout, vq, y, a, stream);
-            if (tap_kernel_for(p, g, MODE) != WINO_TAP_ROWS)
-                return launch_small_auto<4>(p, g, layout, vq, y, a, stream);
+            if (p->m == 2) return launch_small_auto<2, MODE>(p, g, layout, vq, y, aux, a, stream);
+            if (tap_kernel_for(p, g, 0) != WINO_TAP_ROWS)
+                return launch_small_auto<4, MODE>(p, g, layout, vq, y, aux, a, stream);
+            return launch_rows_auto<MODE>(p, g, layout, vq, y, aux, a, stream);
         }
     }
     if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
@@ -1645,8 +1782,7 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
                                        p->uq_dev, vq, p->bias_dev, y, a);
                 return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
             }
-            return p->cin_pad == kKStep ? launch_rows<RwNarrow, true>(p, g, layout, vq, y, a, stream)
-                                        : launch_rows<RwWide, false>(p, g, layout, vq, y, a, stream);
+            return launch_rows_auto<0>(p, g, layout, vq, y, aux, a, stream);
         }
         case WINO_TAP_WAVES: {
             const long long wblocks = (long long)(p->cout_pad / WS_CO) * (g.t_pad / WS_TL);
@@ -1701,16 +1837,11 @@ wino_status check_common(const wino_f4_plan_s* p, const void* x, int32_t n, int3
 }
 
 // K1 for the plan's transform and Winograd-domain width
-template <int MODE>
 wino_status run_k1(int m, int bits, const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq,
-                   int* tapmax, hipStream_t stream) {
-    if constexpr (MODE == 0) {
-        if (bits == 10)
-            return m == 2 ? launch_k1<2, MODE, 10>(a, layout, x, vq, tapmax, stream)
-                          : launch_k1<4, MODE, 10>(a, layout, x, vq, tapmax, stream);
-    }
-    return m == 2 ? launch_k1<2, MODE>(a, layout, x, vq, tapmax, stream)
-                  : launch_k1<4, MODE>(a, layout, x, vq, tapmax, stream);
+                   hipStream_t stream) {
+    if (bits == 10)
+        return m == 2 ? launch_k1<2, 10>(a, layout, x, vq, stream) : launch_k1<4, 10>(a, layout, x, vq, stream);
+    return m == 2 ? launch_k1<2, 8>(a, layout, x, vq, stream) : launch_k1<4, 8>(a, layout, x, vq, stream);
 }
 
 int cexp_int(unsigned long long a, int bits = 8) {
@@ -1795,7 +1926,7 @@ extern "C" wino_status wino_f4_conv_int8(wino_f4_plan_t p, const int8_t* x, int8
     }
     if (!ws || ws_bytes < vq_bytes(p, g)) return WINO_EWORKSPACE;
     int8_t* vq = (int8_t*)ws;
-    st = run_k1<0>(p->m, p->bits, split_k1_args(p, g, ws, ws_bytes), layout, x, vq, nullptr, stream);
+    st = run_k1(p->m, p->bits, split_k1_args(p, g, ws, ws_bytes), layout, x, vq, stream);
     if (st != WINO_OK) return st;
     return launch_k2<0>(p, g, layout, vq, y, nullptr, stream, ws_bytes);
 }
@@ -1845,7 +1976,7 @@ extern "C" wino_status wino_f4_conv_int8_noalloc(wino_f4_plan_t p, const int8_t*
     // channels meet zero Uq rows, padded tiles are never stored), so the
     // scratch needs no clearing between calls
     int8_t* vq = (int8_t*)ws;
-    st = run_k1<0>(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, vq, nullptr, stream);
+    st = run_k1(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, vq, stream);
     if (st != WINO_OK) return st;
     return launch_k2<0>(p, g, layout, vq, y, nullptr, stream);
 }
@@ -1858,7 +1989,7 @@ extern "C" wino_status wino_f4_input_transform(wino_f4_plan_t p, const int8_t* x
     if (st != WINO_OK) return st;
     if (g.ntiles == 0) return WINO_OK;
     if (!ws || ws_bytes < vq_bytes(p, g)) return WINO_EWORKSPACE;
-    return run_k1<0>(p->m, p->bits, split_k1_args(p, g, ws, ws_bytes), layout, x, (int8_t*)ws, nullptr, stream);
+    return run_k1(p->m, p->bits, split_k1_args(p, g, ws, ws_bytes), layout, x, (int8_t*)ws, stream);
 }
 
 extern "C" wino_status wino_f4_tap_gemm(wino_f4_plan_t p, void* ws, size_t ws_bytes, int8_t* y, int32_t n,
@@ -1887,11 +2018,11 @@ static wino_status calibrate_input(int m, int bits, const int8_t* x, int32_t n, 
     int host[kTaps] = {0};
     if (g.ntiles > 0) {
         int* dmax = nullptr;
-        if (hipMalloc(&dmax, sizeof(int) * kTaps) != hipSuccess) return WINO_ENOMEM;
+        if (hipMalloc(&dmax, sizeof(int) * kTaps * (1 + kAbsmaxGroups)) != hipSuccess) return WINO_ENOMEM;
         TapTables tab = {};
-        bool ok = hipMemsetAsync(dmax, 0, sizeof(int) * kTaps, stream) == hipSuccess;
-        if (ok) ok = run_k1<1>(m, 8, k1_args(g, cin, (int)round_up(cin, kKStep), tab), layout, x, nullptr, dmax,
-                               stream) == WINO_OK;
+        const K1Args a = k1_args(g, cin, (int)round_up(cin, kKStep), tab);
+        bool ok = (m == 2 ? launch_absmax<2>(a, layout, x, dmax, dmax + kTaps, stream)
+                          : launch_absmax<4>(a, layout, x, dmax, dmax + kTaps, stream)) == WINO_OK;
         if (ok) ok = hipMemcpyAsync(host, dmax, sizeof(int) * kTaps, hipMemcpyDeviceToHost, stream) == hipSuccess;
         if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
         (void)hipFree(dmax);
@@ -1943,8 +2074,8 @@ extern "C" wino_status wino_f4_calibrate_output(wino_f4_plan_t p, const int8_t* 
         unsigned long long* dmax = nullptr;
         if (hipMalloc(&dmax, sizeof(unsigned long long)) != hipSuccess) return WINO_ENOMEM;
         bool ok = hipMemsetAsync(dmax, 0, sizeof(unsigned long long), stream) == hipSuccess;
-        if (ok) ok = run_k1<0>(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws,
-                               nullptr, stream) == WINO_OK;
+        if (ok) ok = run_k1(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws,
+                            stream) == WINO_OK;
         if (ok) ok = launch_k2<1>(p, g, layout, (const int8_t*)ws, nullptr, dmax, stream) == WINO_OK;
         if (ok) ok = hipMemcpyAsync(&host, dmax, sizeof(host), hipMemcpyDeviceToHost, stream) == hipSuccess;
         if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
@@ -1965,7 +2096,7 @@ extern "C" wino_status wino_f4_debug_input_transform(wino_f4_plan_t p, const int
     if (!vq_out) return WINO_EINVAL;
     if (g.ntiles == 0) return WINO_OK;
     if (!ws || ws_bytes < vq_bytes(p, g)) return WINO_EWORKSPACE;
-    st = run_k1<0>(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws, nullptr, stream);
+    st = run_k1(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws, stream);
     if (st != WINO_OK) return st;
     // compact [ntap][cin_pad/kpr][t_pad][kpr] -> [ntap][ntiles][cin] (elements
     // of es bytes: int8, or fp16 for 10-bit plans), one 2-D copy per (tap, k row)
@@ -1993,7 +2124,7 @@ extern "C" wino_status wino_f4_debug_tap_gemm(wino_f4_plan_t p, const int8_t* x,
     if (!m_out) return WINO_EINVAL;
     if (g.ntiles == 0) return WINO_OK;
     if (!ws || ws_bytes < vq_bytes(p, g)) return WINO_EWORKSPACE;
-    st = run_k1<0>(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws, nullptr, stream);
+    st = run_k1(p->m, p->bits, k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits), layout, x, (int8_t*)ws, stream);
     if (st != WINO_OK) return st;
     return launch_k2<2>(p, g, layout, (const int8_t*)ws, nullptr, m_out, stream);
 }

@@ -77,10 +77,25 @@ __device__ __forceinline__ void lds_copy16_half(const void* base, uint32_t lane_
 }
 
 // ONE: a single 64-channel chunk (Cin <= 64)
-template <class C, int LAYOUT, bool ONE>
+// maximum of zmax over the workgroup's W waves into *out, one atomic
+template <int W>
+__device__ __forceinline__ void block_max(uint32_t zmax, uint32_t* lds, unsigned long long* out) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) zmax = max(zmax, (uint32_t)__shfl_xor((int)zmax, off, 64));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = zmax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < W; ++w) zmax = max(zmax, lds[w]);
+        atomicMax(out, (unsigned long long)zmax);
+    }
+}
+
+// MODE 0: store y.  MODE 1: max |Y + bias| into *aux (calibration).
+template <class C, int LAYOUT, bool ONE, int MODE>
 __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
     const int8_t* __restrict__ uq, const int8_t* __restrict__ vq, const int32_t* __restrict__ bias,
-    int8_t* __restrict__ y, K2Args g) {
+    int8_t* __restrict__ y, void* __restrict__ aux, K2Args g) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[C::NBUF * C::STAGE];
     __shared__ __attribute__((aligned(16))) int bias_blk[RW_CO];
     const int lane = threadIdx.x & 63;
@@ -158,7 +173,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
     const int row_a = 16 * RW_CB * cw + lr, row_b = RW_CO + 16 * tw + lr;
     const int frag_a = row_a * 64 + 16 * lds_slot(row_a, lk);   // block c: + 16 c rows
     const int frag_b = row_b * 64 + 16 * lds_slot(row_b, lk);
-    const int rnd = g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
+    const int rnd = MODE == 0 && g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
 
     // value k = 4 c + r of a lane: channel 16 (RW_CB cw + c) + 4 lk + r of tile
     // 16 tw + lr
@@ -169,7 +184,24 @@ __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
     // (i, j), packed pair by pair; NCHW: word 4 c + r = the pixels of channel r.
     int prev[2][4];
     uint32_t half[2][4];
+    uint32_t zmax = 0, in_row[4], in_col[4];               // MODE 1: masks of the lane's tile's pixels
+    if constexpr (MODE == 1) {
+        const long long tile = tl_blk + 16 * tw + lr;
+        int img = 0, ty = 0, tx = 0;
+        if (tile < g.ntiles) tile_coords(tile, g, img, ty, tx);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            in_row[i] = tile < g.ntiles && 4 * ty + i < g.h ? ~0u : 0u;
+            in_col[i] = 4 * tx + i < g.w ? ~0u : 0u;
+        }
+    }
     auto put = [&](int i, int slot, int c, int r, const int (&v)[4]) __attribute__((always_inline)) {
+        if constexpr (MODE == 1) {                         // channels past Cout hold zeros
+#pragma unroll
+            for (int j = 0; j < 4; ++j) zmax = max(zmax, (uint32_t)abs(v[j]) & in_row[i] & in_col[j]);
+            asm volatile("" : "+v"(zmax));
+            return;
+        }
         if (LAYOUT == WINO_NCHW) {
             out[i][4 * c + r] = join2(requant2(v[0], v[1], g.out_shift), requant2(v[2], v[3], g.out_shift));
             asm volatile("" : "+v"(out[i][4 * c + r]));
@@ -342,6 +374,11 @@ __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
 #undef RW_ROW
 #pragma unroll
     for (int k = 0; k < RW_V; ++k) fold(std::integral_constant<int, 5>{}, mb, k >> 2, k & 3);
+    if constexpr (MODE == 1) {
+        __syncthreads();                                   // every wave is done reading the ring
+        block_max<C::WAVES>(zmax, (uint32_t*)lds, (unsigned long long*)aux);
+        return;
+    }
     if (g.relu)
 #pragma unroll
         for (int i = 0; i < 4; ++i)

@@ -31,11 +31,13 @@ struct TsCfg {
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 
-template <int M, int CB, int TB, int LAYOUT>
+// MODE 0: store y.  MODE 1: max |Y + bias| into *aux (calibration).
+template <int M, int CB, int TB, int LAYOUT, int MODE>
 __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int8_t* __restrict__ uq,
-                                                                    const int8_t* __restrict__ vq,
-                                                                    const int32_t* __restrict__ bias,
-                                                                    int8_t* __restrict__ y, K2Args g) {
+                                                                       const int8_t* __restrict__ vq,
+                                                                       const int32_t* __restrict__ bias,
+                                                                       int8_t* __restrict__ y,
+                                                                       void* __restrict__ aux, K2Args g) {
     typedef TsCfg<M, CB, TB> C;
     constexpr int N = C::N;
     __shared__ __attribute__((aligned(16))) int zs[N][M][C::TL][C::PITCH];
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
     for (int b = 0; b < N; ++b) load(b);
     // bias plus rounding constant, injected through tap (1,1): its row and
     // column of A^T are all ones, so it reaches every output of the tile once
-    const int rnd = g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
+    const int rnd = MODE == 0 && g.out_shift > 0 ? 1 << (g.out_shift - 1) : 0;
     v4i bias_rnd[CB];
 #pragma unroll
     for (int c = 0; c < CB; ++c) bias_rnd[c] = *(const v4i*)(bias + co_blk + 16 * c + 4 * lk) + rnd;
@@ -128,6 +130,7 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
         // four channels each
         const bool word = (g.cout & 3) == 0 && ((uintptr_t)y & 3) == 0;
         constexpr int QC = C::CO / 4;
+        uint32_t zmax = 0;
         for (int id = threadIdx.x; id < C::TL * M * QC; id += C::THREADS) {
             const int q = id % QC, j = id / QC % M, tl = id / (QC * M);
             const long long tile = tl_blk + tl;
@@ -152,6 +155,11 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if (M * ty + i >= g.h) break;
+                if constexpr (MODE == 1) {                 // channels past Cout hold zeros
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) zmax = max(zmax, (uint32_t)abs(o[r][i]));
+                    continue;
+                }
                 uint32_t w = join2(requant2(o[0][i], o[1][i], g.out_shift), requant2(o[2][i], o[3][i], g.out_shift));
                 if (g.relu) w = relu4(w);
                 if (word) {
@@ -163,6 +171,10 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
                 }
                 p += (long long)g.w * g.cout;
             }
+        }
+        if constexpr (MODE == 1) {
+            __syncthreads();                               // zs is read no more
+            block_max<C::THREADS / 64>(zmax, (uint32_t*)zs, (unsigned long long*)aux);
         }
     } else {
         // one item per (channel, tile), tiles fastest: M rows of M pixels
