@@ -149,15 +149,16 @@ def _dptr(t, dtype, need=0, what="tensor"):
     import torch
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{what}: expected a torch tensor on the GPU, got {type(t).__name__}")
+    # plain addresses: the argument types of the C functions convert them
+    if t.is_cuda and (dtype is None or t.dtype == dtype) and t.is_contiguous() and (need <= 0 or t.numel() >= need):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{what}: must be a GPU tensor (the kernels read and write device memory)")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{what}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{what}: must be contiguous")
-    if need > 0 and t.numel() < need:
-        raise ValueError(f"{what}: holds {t.numel()} elements, the call reads or writes {need}")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{what}: holds {t.numel()} elements, the call reads or writes {need}")
 
 
 def _tiles(n, h, w, m):
@@ -177,13 +178,23 @@ def _elems(*dims):
     return p
 
 
+_RAW_STREAM = None
+
+
 def _stream(stream):
     if stream is None:
+        # the raw handle without torch's Stream object around it: 0.4 us
+        # instead of 2.8 of a call's ~12 us of host time
+        global _RAW_STREAM
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _RAW_STREAM is None:
+            torch.cuda.current_stream()          # initializes the device state
+            _RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+                lambda device: torch.cuda.current_stream(device).cuda_stream)
+        return _RAW_STREAM(torch.cuda.current_device())
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _nbytes(t):
