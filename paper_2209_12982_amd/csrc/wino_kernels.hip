@@ -1122,6 +1122,7 @@ __global__ __launch_bounds__(KR_THREADS) void wino_tap_gemm_rows_sk(const int8_t
 
 #include "wino_tap_rows.h"
 #include "wino_tap_small.h"
+#include "wino_conv_small.h"
 #include "wino_tap_ws.h"
 
 // ---------------------------------------------------------------------------
@@ -1697,11 +1698,7 @@ wino_status launch_small_auto(const wino_f4_plan_s* p, const Geometry& g, wino_l
     return launch_small<M, 1, 1, MODE>(p, g, layout, vq, y, aux, a, stream);
 }
 
-// ws_bytes: the workspace at vq (the stream-K split uses the part past Vq)
-template <int MODE>
-wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
-                      int8_t* y, void* aux, hipStream_t stream, size_t ws_bytes = 0) {
-    if (g.ntiles == 0) return WINO_OK;
+K2Args k2_args(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* y) {
     K2Args a;
     a.cin_pad = p->cin_pad;
     a.cout = p->cout;
@@ -1728,6 +1725,15 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
         a.shrow[r] = 0;
         for (int b = 0; b < 6 && 6 * r + b < p->ntap; ++b) a.shrow[r] |= (uint32_t)(p->sh[6 * r + b] & 31) << (5 * b);
     }
+    return a;
+}
+
+// ws_bytes: the workspace at vq (the stream-K split uses the part past Vq)
+template <int MODE>
+wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
+                      int8_t* y, void* aux, hipStream_t stream, size_t ws_bytes = 0) {
+    if (g.ntiles == 0) return WINO_OK;
+    K2Args a = k2_args(p, g, layout, y);
     if (p->bits == 10) {
         if (p->m == 2) return launch_resident<K2F2_10, 2, MODE, 10>(p, g, layout, vq, y, aux, a, stream);
         switch (tap_kernel_for(p, g, MODE)) {
@@ -1844,6 +1850,64 @@ wino_status run_k1(int m, int bits, const K1Args& a, wino_layout layout, const i
     return m == 2 ? launch_k1<2, 8>(a, layout, x, vq, stream) : launch_k1<4, 8>(a, layout, x, vq, stream);
 }
 
+template <int M, int CB>
+wino_status launch_conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,
+                              CsArgs a, hipStream_t stream) {
+    const int nco = (p->cout + 16 * CB - 1) / (16 * CB);
+    const long long nb = (long long)nco * ((g.ntiles + 15) / 16);
+    a.k.nblocks = (int)nb;
+    a.k.dgco = make_fastdiv((uint32_t)nco);
+    const dim3 grid((unsigned)nb), block(64 * (M + 2));
+#define CS_LAUNCH(L, S) \
+    hipLaunchKernelGGL((wino_conv_small<M, CB, L, S>), grid, block, 0, stream, x, p->uq_dev, p->bias_dev, y, a)
+    if (layout == WINO_NHWC) {
+        if (a.q_sat) CS_LAUNCH(WINO_NHWC, true); else CS_LAUNCH(WINO_NHWC, false);
+    } else {
+        if (a.q_sat) CS_LAUNCH(WINO_NCHW, true); else CS_LAUNCH(WINO_NCHW, false);
+    }
+#undef CS_LAUNCH
+    return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
+}
+
+// The convolution in one launch (wino_conv_small) where that is faster than the
+// input transform and the small tap GEMM; false: not taken.  The block takes the
+// most channels (64, 32, 16) that leave 5/8 of the compute units a block.  The
+// limits: every block of output channels repeats the transform, and a block
+// walks its 64-channel chunks one after another (us of kernel time, one launch
+// against the two: F2 1x16->16 32x32 NCHW 6.3 / 7.6, 8x64->64 56x56 8.4 / 11.0,
+// 8x256->256 14x14 9.1 / 10.6, 8x128->256 28x28 10.6 / 12.4, 8x64->128 56x56 13.3 /
+// 14.1; F4 1x64->64 28x28 7.8 / 9.3, 8x128->128 32x32 10.7 / 10.7, and one launch
+// less; 1x240->64 21x27 15.6 / 12.1).  F4's larger blocks lose to 16 x 16.
+bool conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,
+                hipStream_t stream, wino_status& st) {
+    if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return false;
+    const long long xb = (long long)g.n * g.h * g.w * p->cin;
+    if (xb >= 0x7ffffff0ll || (layout == WINO_NHWC ? p->cin < 4 : g.w < 4) || ((uintptr_t)x & 3) != 0) return false;
+    const long long cus = num_cus(), tb = (g.ntiles + 15) / 16;
+    const int nkc = p->cin_pad / kKStep;
+    auto blocks = [&](int cb) { return tb * ((p->cout + 16 * cb - 1) / (16 * cb)); };
+    int cb = 1;
+    if (p->m == 2) {
+        if (blocks(4) >= cus * 5 / 8) cb = 4;
+        else if (blocks(2) >= cus * 5 / 8) cb = 2;
+        if (blocks(cb) * nkc > 4 * cus) return false;
+    } else if (nkc > 2 || blocks(1) > cus) {
+        return false;
+    }
+    CsArgs a;
+    a.k = k2_args(p, g, layout, y);
+    a.cin = p->cin;
+    a.x_bytes = (int)xb;
+    const K1Args k1 = k1_args(g, p->cin, p->cin_pad, a.k.tab);
+    a.q_sat = k1.q_sat;
+    for (int t = 0; t < kTaps; ++t) a.rnd2[t] = k1.rnd2[t];
+    if (p->m == 4) st = launch_conv_small<4, 1>(p, g, layout, x, y, a, stream);
+    else if (cb == 4) st = launch_conv_small<2, 4>(p, g, layout, x, y, a, stream);
+    else if (cb == 2) st = launch_conv_small<2, 2>(p, g, layout, x, y, a, stream);
+    else st = launch_conv_small<2, 1>(p, g, layout, x, y, a, stream);
+    return true;
+}
+
 int cexp_int(unsigned long long a, int bits = 8) {
     // smallest e >= 0 with a <= 2^(bits-1) * 2^e (callers clamp at 0 anyway)
     int e = 0;
@@ -1925,6 +1989,7 @@ extern "C" wino_status wino_f4_conv_int8(wino_f4_plan_t p, const int8_t* x, int8
         return wino_f4_conv_fused(p, x, y, n, h, w, layout, stream);
     }
     if (!ws || ws_bytes < vq_bytes(p, g)) return WINO_EWORKSPACE;
+    if (conv_small(p, g, layout, x, y, stream, st)) return st;
     int8_t* vq = (int8_t*)ws;
     st = run_k1(p->m, p->bits, split_k1_args(p, g, ws, ws_bytes), layout, x, vq, stream);
     if (st != WINO_OK) return st;

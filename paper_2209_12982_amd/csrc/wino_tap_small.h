@@ -31,6 +31,98 @@ struct TsCfg {
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 
+// The column pass of a block's row-pass results zs (bias and rounding constant
+// included): Y = A^T z, then requantize and store (MODE 0), or the maximum of |Y|
+// over the in-image outputs into zmax (MODE 1).
+template <int M, int CO, int TL, int THREADS, int LAYOUT, int MODE>
+__device__ __forceinline__ void small_column_pass(const int (&zs)[M + 2][M][TL][CO + 4], const K2Args& g,
+                                                  int8_t* __restrict__ y, int co_blk, long long tl_blk, uint32_t& zmax) {
+    constexpr int N = M + 2;
+    if constexpr (LAYOUT == WINO_NHWC) {
+        // column pass, one item per (tile, column j, four channels): M pixels of
+        // four channels each
+        const bool word = (g.cout & 3) == 0 && ((uintptr_t)y & 3) == 0;
+        constexpr int QC = CO / 4;
+        for (int id = threadIdx.x; id < TL * M * QC; id += THREADS) {
+            const int q = id % QC, j = id / QC % M, tl = id / (QC * M);
+            const long long tile = tl_blk + tl;
+            const int co = co_blk + 4 * q;
+            if (tile >= g.ntiles || co >= g.cout) continue;
+            v4i zv[N];
+#pragma unroll
+            for (int b = 0; b < N; ++b) zv[b] = *(const v4i*)&zs[b][j][tl][4 * q];
+            int o[4][M];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                int col[N];
+#pragma unroll
+                for (int b = 0; b < N; ++b) col[b] = zv[b][r];
+                Wino<M>::at(col, o[r]);
+            }
+            int img, ty, tx;
+            tile_coords(tile, g, img, ty, tx);
+            const int xx = M * tx + j;
+            if (xx >= g.w) continue;
+            int8_t* p = y + (((long long)img * g.h + M * ty) * g.w + xx) * g.cout + co;
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                if (M * ty + i >= g.h) break;
+                if constexpr (MODE == 1) {                 // channels past Cout hold zeros
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) zmax = max(zmax, (uint32_t)abs(o[r][i]));
+                    continue;
+                }
+                uint32_t w = join2(requant2(o[0][i], o[1][i], g.out_shift), requant2(o[2][i], o[3][i], g.out_shift));
+                if (g.relu) w = relu4(w);
+                if (word) {
+                    *(uint32_t*)p = w;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (co + r < g.cout) p[r] = (int8_t)(w >> (8 * r));
+                }
+                p += (long long)g.w * g.cout;
+            }
+        }
+    } else {
+        // one item per (channel, tile), tiles fastest: M rows of M pixels
+        const bool word = g.w % M == 0 && ((uintptr_t)y & (M - 1)) == 0;
+        for (int id = threadIdx.x; id < TL * CO; id += THREADS) {
+            const int tl = id % TL, ch = id / TL;
+            const long long tile = tl_blk + tl;
+            const int co = co_blk + ch;
+            if (tile >= g.ntiles || co >= g.cout) continue;
+            int o[M][M];                                   // [column][row]
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                int col[N];
+#pragma unroll
+                for (int b = 0; b < N; ++b) col[b] = zs[b][j][tl][ch];
+                Wino<M>::at(col, o[j]);
+            }
+            int img, ty, tx;
+            tile_coords(tile, g, img, ty, tx);
+            int8_t* p = y + (((long long)img * g.cout + co) * g.h + M * ty) * g.w + M * tx;
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                if (M * ty + i >= g.h) break;
+                uint32_t w = requant2(o[0][i], o[1][i], g.out_shift);
+                if constexpr (M == 4) w = join2(w, requant2(o[2][i], o[3][i], g.out_shift));
+                if (g.relu) w = relu4(w);
+                if (word) {
+                    if constexpr (M == 4) *(uint32_t*)p = w;
+                    else *(uint16_t*)p = (uint16_t)w;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < M; ++j)
+                        if (M * tx + j < g.w) p[j] = (int8_t)(w >> (8 * j));
+                }
+                p += g.w;
+            }
+        }
+    }
+}
+
 // MODE 0: store y.  MODE 1: max |Y + bias| into *aux (calibration).
 template <int M, int CB, int TB, int LAYOUT, int MODE>
 __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int8_t* __restrict__ uq,
@@ -125,92 +217,10 @@ __global__ __launch_bounds__(64 * (M + 2), 2) void wino_tap_gemm_small(const int
         }
     __syncthreads();
 
-    if constexpr (LAYOUT == WINO_NHWC) {
-        // column pass, one item per (tile, column j, four channels): M pixels of
-        // four channels each
-        const bool word = (g.cout & 3) == 0 && ((uintptr_t)y & 3) == 0;
-        constexpr int QC = C::CO / 4;
-        uint32_t zmax = 0;
-        for (int id = threadIdx.x; id < C::TL * M * QC; id += C::THREADS) {
-            const int q = id % QC, j = id / QC % M, tl = id / (QC * M);
-            const long long tile = tl_blk + tl;
-            const int co = co_blk + 4 * q;
-            if (tile >= g.ntiles || co >= g.cout) continue;
-            v4i zv[N];
-#pragma unroll
-            for (int b = 0; b < N; ++b) zv[b] = *(const v4i*)&zs[b][j][tl][4 * q];
-            int o[4][M];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int col[N];
-#pragma unroll
-                for (int b = 0; b < N; ++b) col[b] = zv[b][r];
-                Wino<M>::at(col, o[r]);
-            }
-            int img, ty, tx;
-            tile_coords(tile, g, img, ty, tx);
-            const int xx = M * tx + j;
-            if (xx >= g.w) continue;
-            int8_t* p = y + (((long long)img * g.h + M * ty) * g.w + xx) * g.cout + co;
-#pragma unroll
-            for (int i = 0; i < M; ++i) {
-                if (M * ty + i >= g.h) break;
-                if constexpr (MODE == 1) {                 // channels past Cout hold zeros
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) zmax = max(zmax, (uint32_t)abs(o[r][i]));
-                    continue;
-                }
-                uint32_t w = join2(requant2(o[0][i], o[1][i], g.out_shift), requant2(o[2][i], o[3][i], g.out_shift));
-                if (g.relu) w = relu4(w);
-                if (word) {
-                    *(uint32_t*)p = w;
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (co + r < g.cout) p[r] = (int8_t)(w >> (8 * r));
-                }
-                p += (long long)g.w * g.cout;
-            }
-        }
-        if constexpr (MODE == 1) {
-            __syncthreads();                               // zs is read no more
-            block_max<C::THREADS / 64>(zmax, (uint32_t*)zs, (unsigned long long*)aux);
-        }
-    } else {
-        // one item per (channel, tile), tiles fastest: M rows of M pixels
-        const bool word = g.w % M == 0 && ((uintptr_t)y & (M - 1)) == 0;
-        for (int id = threadIdx.x; id < C::TL * C::CO; id += C::THREADS) {
-            const int tl = id % C::TL, ch = id / C::TL;
-            const long long tile = tl_blk + tl;
-            const int co = co_blk + ch;
-            if (tile >= g.ntiles || co >= g.cout) continue;
-            int o[M][M];                                   // [column][row]
-#pragma unroll
-            for (int j = 0; j < M; ++j) {
-                int col[N];
-#pragma unroll
-                for (int b = 0; b < N; ++b) col[b] = zs[b][j][tl][ch];
-                Wino<M>::at(col, o[j]);
-            }
-            int img, ty, tx;
-            tile_coords(tile, g, img, ty, tx);
-            int8_t* p = y + (((long long)img * g.cout + co) * g.h + M * ty) * g.w + M * tx;
-#pragma unroll
-            for (int i = 0; i < M; ++i) {
-                if (M * ty + i >= g.h) break;
-                uint32_t w = requant2(o[0][i], o[1][i], g.out_shift);
-                if constexpr (M == 4) w = join2(w, requant2(o[2][i], o[3][i], g.out_shift));
-                if (g.relu) w = relu4(w);
-                if (word) {
-                    if constexpr (M == 4) *(uint32_t*)p = w;
-                    else *(uint16_t*)p = (uint16_t)w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < M; ++j)
-                        if (M * tx + j < g.w) p[j] = (int8_t)(w >> (8 * j));
-                }
-                p += g.w;
-            }
-        }
+    uint32_t zmax = 0;
+    small_column_pass<M, C::CO, C::TL, C::THREADS, LAYOUT, MODE>(zs, g, y, co_blk, tl_blk, zmax);
+    if constexpr (MODE == 1) {
+        __syncthreads();                                   // zs is read no more
+        block_max<C::THREADS / 64>(zmax, (uint32_t*)zs, (unsigned long long*)aux);
     }
 }

@@ -1,6 +1,7 @@
-"""The small-layer tap GEMM (one wave per row of taps) against the CPU oracle,
-bit for bit: each of its block shapes at ragged tile and channel counts, one
-and several 64-channel chunks, channel blocks that leave a partial group, both
+"""The small-layer kernels (one wave per row of taps) against the CPU oracle, bit
+for bit: the tap GEMM behind the input transform, and the convolution in one
+launch; each of their block shapes at ragged tile and channel counts, one and
+several 64-channel chunks, channel blocks that leave a partial group, both
 transforms and layouts."""
 import numpy as np
 import pytest
@@ -9,7 +10,7 @@ import paper_2209_12982_amd as W
 import workloads
 from oracle import tapwise
 
-from gpu_util import run_conv, torch_dev
+from gpu_util import empty_out, from_device_nchw, run_conv, to_device, torch_dev, workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +39,40 @@ def test_small_tap_gemm(shape, m, layout):
     gp = (W.wino_f4_plan if m == 4 else W.wino_f2_plan)(f, eb, bias=b, out_shift=10, relu=relu)
     assert W.wino_f4_plan_info(gp)["epilogue_bits"] == 32 and spec.m == m
     assert W.wino_f4_tap_kernel_choice(gp, n, h, w) == W.TAP_RESIDENT_64X32
+    xd, y, ws = to_device(x, layout), empty_out(n, cout, h, w, layout), workspace(gp, n, h, w)
+    W.wino_f4_input_transform(gp, xd, n, h, w, layout, ws)
+    W.wino_f4_tap_gemm(gp, ws, y, n, h, w, layout)
+    ref = tapwise.conv_int8(x, op)
+    got = from_device_nchw(y, layout)
+    assert (got == ref).all(), f"tap GEMM: {(got != ref).sum()} mismatches"
+    got = run_conv(gp, x, layout)
+    assert (got == ref).all(), f"convolution: {(got != ref).sum()} mismatches"
+
+
+# n, cin, cout, h, w, e_B offset: the one-launch convolution with 64, 32 and 16
+# channels a block, words shifted inside pixels and rows, the image's last bytes,
+# the shift-and-clamp requantization, up to four chunks
+ONE_LAUNCH = [
+    (10, 5, 50, 31, 32, 0),      # F2: 160 blocks of 64 channels
+    (2, 130, 200, 27, 28, 0),    # F2: 25 x 7 blocks of 32 channels, three chunks
+    (1, 200, 20, 4, 4, 0),       # F2: one tile block, four chunks
+    (1, 67, 33, 13, 5, 4),       # e_B past the one-instruction form
+    (3, 64, 16, 6, 7, 0),
+    (1, 3, 9, 9, 3, 0),          # below four channels (NHWC) and columns (NCHW): two launches
+]
+
+
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+@pytest.mark.parametrize("m", [4, 2])
+@pytest.mark.parametrize("shape", ONE_LAUNCH)
+def test_one_launch_convolution(shape, m, layout):
+    n, cin, cout, h, w, off = shape
+    x, f, b = workloads.random_case(33, n, cin, cout, h, w, signed=True)
+    x.reshape(-1)[-3:] = [-128, 127, -128]
+    eb = [e + off for e in tapwise.calibrate_input_exps(x, m=m)]
+    assert off == 0 or max(eb) > 8 or m == 2
+    op = tapwise.make_plan(f, eb, bias=b, out_shift=9, relu=off > 0, m=m)
+    gp = (W.wino_f4_plan if m == 4 else W.wino_f2_plan)(f, eb, bias=b, out_shift=9, relu=off > 0)
     y = run_conv(gp, x, layout)
     ref = tapwise.conv_int8(x, op)
     assert (y == ref).all(), f"{(y != ref).sum()} mismatches"
