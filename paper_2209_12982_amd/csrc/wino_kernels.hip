@@ -1195,16 +1195,16 @@ __global__ __launch_bounds__(KW_THREADS) void wino_tap_gemm_rows_wide(const int8
         dsto[i] = b * KW_CHUNK + q * 1024;
     }
     int next_kc = 0, next_buf = 0;
-    auto issue_next = [&]() {
-        uint8_t* d = lds + next_buf * KW_STAGE;
-        const bool row_end = ++next_kc == nkc;
-        if (row_end) next_kc = 0;
-#pragma unroll
-        for (int i = 0; i < KW_LPW; ++i) {
-            lds_copy16(src[i] + lane_off, (__attribute__((address_space(3))) void*)(d + dsto[i]));
-            src[i] += row_end ? radv[i] : kadv[i];
+    bool row_end = false;
+    // load i of the next stage; load 0 opens it, load KW_LPW - 1 closes it
+    auto issue = [&](int i) __attribute__((always_inline)) {
+        if (i == 0) {
+            row_end = ++next_kc == nkc;
+            if (row_end) next_kc = 0;
         }
-        next_buf = next_buf == KW_NBUF - 1 ? 0 : next_buf + 1;
+        lds_copy16(src[i] + lane_off, (__attribute__((address_space(3))) void*)(lds + next_buf * KW_STAGE + dsto[i]));
+        src[i] += row_end ? radv[i] : kadv[i];
+        if (i == KW_LPW - 1) next_buf = next_buf == KW_NBUF - 1 ? 0 : next_buf + 1;
     };
 
     // compute side
@@ -1225,12 +1225,18 @@ __global__ __launch_bounds__(KW_THREADS) void wino_tap_gemm_rows_wide(const int8
 
 #pragma unroll
     for (int st = 0; st < KW_NBUF - 1; ++st)
-        if (st < nstage) issue_next();
+#pragma unroll
+        for (int i = 0; i < KW_LPW; ++i) issue(i);          // nstage >= 12
     int s = 0, buf = 0;
 #pragma unroll
     for (int a = 0; a < 6; ++a) {
         v4i m[6];
-        auto stage = [&](bool first) {
+        v4f f[6];
+        // k rows come in pairs (64 channels).  fp16 10-bit integers: a pair's 64
+        // products are at most 2^18, so every partial sum is an integer of at
+        // most 2^24, exact in fp32; the second row of a pair accumulates on the
+        // first and goes to int32 once.
+        auto stage = [&](bool first, bool second) __attribute__((always_inline)) {
             // stage s has landed once only the stages issued after it are
             // pending: min(NBUF - 2, nstage - 1 - s) of them
             const int ahead = min(KW_NBUF - 2, nstage - 1 - s);
@@ -1241,7 +1247,9 @@ __global__ __launch_bounds__(KW_THREADS) void wino_tap_gemm_rows_wide(const int8
             else
                 WINO_WAIT_VM_LDS(0);
             ring_barrier();   // stage s visible; stage s-1 (the buffer refilled next) consumed
-            if (s + KW_NBUF - 1 < nstage) issue_next();
+            // copies between the MFMAs, one per tap: in a row they keep the waves
+            // from computing while the load path takes them
+            const bool more = s + KW_NBUF - 1 < nstage;
             const uint8_t* base = lds + buf * KW_STAGE;
             buf = buf == KW_NBUF - 1 ? 0 : buf + 1;
             ++s;
@@ -1252,26 +1260,29 @@ __global__ __launch_bounds__(KW_THREADS) void wino_tap_gemm_rows_wide(const int8
             };
             frag(0);
             frag(1);
-            const v4i zero = (v4i){0, 0, 0, 0};
 #pragma unroll
             for (int b = 0; b < 6; ++b) {
-                if constexpr (Q == 10) {
-                    // fp16 10-bit integers: 32 products and their sums are
-                    // integers below 2^24, exact in fp32
-                    const v4f r = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        __builtin_bit_cast(v8h, fa[b & 1]), __builtin_bit_cast(v8h, fb[b & 1]),
-                        (v4f){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                static_assert(Q == 10, "fp16 operands");
+                const v4f r = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(v8h, fa[b & 1]), __builtin_bit_cast(v8h, fb[b & 1]),
+                    second ? f[b] : (v4f){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                if (more && b < KW_LPW) issue(b);
+                if (b + 2 < 6) frag(b + 2);
+                if (second) {
                     const v4i ri = __builtin_convertvector(r, v4i);
                     m[b] = first ? ri
                                  : __builtin_bit_cast(v4i, __builtin_bit_cast(v4u, m[b]) + __builtin_bit_cast(v4u, ri));
                 } else {
-                    m[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[b & 1], fb[b & 1], first ? zero : m[b], 0, 0, 0);
+                    f[b] = r;
                 }
-                if (b + 2 < 6) frag(b + 2);
             }
         };
-        stage(true);
-        for (int kc = 1; kc < nkc; ++kc) stage(false);
+        stage(true, false);
+        stage(true, true);
+        for (int kc = 2; kc < nkc; kc += 2) {
+            stage(false, false);
+            stage(false, true);
+        }
 
         // fold row a: z = (M'[a, :]) A, then Y += A^T[:, a] z, in YT
 #pragma unroll
