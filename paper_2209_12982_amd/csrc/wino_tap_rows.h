@@ -422,6 +422,22 @@ __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(
                     __builtin_nontemporal_store(
                         d[i], (v4i*)(y + (((long long)img * g.h + yy) * g.w + xx) * g.cout + co_blk + 16 * q));
             }
+        } else if ((g.cout & 3) == 0 && ((uintptr_t)y & 3) == 0) {
+            // words of four channels: lane = word lane % 16 of pixel 4 k + lane / 16
+            const int q = lane & 15;
+            const bool co_ok = co_blk + 4 * q < g.cout;
+            for (int tl = wave; tl < C::TL; tl += C::WAVES) {
+                const long long tile = tl_blk + tl;
+                if (tile >= g.ntiles) break;
+                int img, ty, tx;
+                tile_coords(tile, g, img, ty, tx);
+                const int xx = 4 * tx + (lane >> 4);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (4 * ty + k < g.h && xx < g.w && co_ok)
+                        *(uint32_t*)(y + (((long long)img * g.h + 4 * ty + k) * g.w + xx) * g.cout + co_blk + 4 * q) =
+                            *(const uint32_t*)(lds + tl * PITCH + 64 * (4 * k + (lane >> 4)) + 4 * q);
+            }
         } else {
             // any Cout and alignment: lane = channel, one pixel per store
             const int co = co_blk + lane;
