@@ -14,7 +14,12 @@
 //                         applies Y = A^T M A, adds bias, requantizes and
 //                         stores int8 (Sec. III rearranged scheme; the
 //                         out_xform / dconv / write steps of the operator
-//                         dataflow, Sec. IV-B2).
+//                         dataflow, Sec. IV-B2).  wino_tap_gemm_rows
+//                         (wino_tap_rows.h) for large F4 layers,
+//                         wino_tap_gemm_small (wino_tap_small.h) for F2 and
+//                         small F4 ones.
+//   wino_conv_small       both in one launch for small layers
+//                         (wino_conv_small.h).
 //
 // Bit exactness: all arithmetic is integer.  B^T d B of int8 data is at most
 // 12768 in magnitude and every intermediate of its row pass at most 1278, so
@@ -1699,6 +1704,16 @@ wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout
 // 8.7 [64] 6.7 [128] 5.6 [256]; 256->512 13.8 [256] 18.3 [512] 21.9 [1024]; F4
 // 2x75x75 256->256 16.1 [184] 20.2 [368] 17.9 [736]; F2 8x14x14 256->256 7.8
 // [104] 6.2 [208] 6.7 [400]; F2 8x56x56 64->64 5.7 [392] 5.6 [784] 6.6 [1568]).
+// F2 from 256 input channels on, where 32x32 blocks need more than one round of the
+// compute units and the tap-resident kernel's 64x32 blocks do not, keeps the latter
+// (8x256->512 20x20: 14.0 against 16.8 us for the layer, 4x256->256 40x40: 14.5
+// against 15.4; with fewer channels, or more or fewer blocks, the small-layer
+// kernel is ahead).
+bool f2_wide_blocks(const wino_f4_plan_s* p, const Geometry& g) {
+    const long long cus = num_cus(), t32 = (g.ntiles + 31) / 32;
+    return p->cin_pad >= 4 * kKStep && t32 * ((p->cout + 31) / 32) > cus && t32 * (p->cout_pad / 64) <= cus;
+}
+
 template <int M, int MODE>
 wino_status launch_small_auto(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
                               int8_t* y, void* aux, const K2Args& a, hipStream_t stream) {
@@ -1766,7 +1781,9 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
     // the row-streamed kernel's sizes on, and the small-layer kernel
     if constexpr (MODE <= 1) {
         if (p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO) {
-            if (p->m == 2) return launch_small_auto<2, MODE>(p, g, layout, vq, y, aux, a, stream);
+            if (p->m == 2 && !f2_wide_blocks(p, g))
+                return launch_small_auto<2, MODE>(p, g, layout, vq, y, aux, a, stream);
+            if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
             if (tap_kernel_for(p, g, 0) != WINO_TAP_ROWS)
                 return launch_small_auto<4, MODE>(p, g, layout, vq, y, aux, a, stream);
             return launch_rows_auto<MODE>(p, g, layout, vq, y, aux, a, stream);

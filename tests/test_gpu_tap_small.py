@@ -78,6 +78,18 @@ def test_one_launch_convolution(shape, m, layout):
     assert (y == ref).all(), f"{(y != ref).sum()} mismatches"
 
 
+def test_f2_wide_blocks():
+    """The F2 sizes that keep the 64x32 tap-resident blocks under AUTO."""
+    torch_dev()
+    n, cin, cout, h, w = 8, 200, 510, 20, 20
+    x, f, b = workloads.random_case(34, n, cin, cout, h, w, signed=True)
+    eb = tapwise.calibrate_input_exps(x, m=2)
+    op = tapwise.make_plan(f, eb, bias=b, out_shift=10, m=2)
+    gp = W.wino_f2_plan(f, eb, bias=b, out_shift=10)
+    for layout in (W.NCHW, W.NHWC):
+        assert (run_conv(gp, x, layout) == tapwise.conv_int8(x, op)).all()
+
+
 @pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
 def test_small_tap_gemm_unaligned_output(layout):
     """An output that is not 4-byte aligned takes the byte stores."""
