@@ -1462,8 +1462,17 @@ wino_status launch_k1(const K1Args& a, wino_layout layout, const int8_t* x, int8
     return launch_k1_band<M, WINO_NCHW, Q, K1_TX>(a, x, vq, stream);
 }
 
+// Blocks that wino_input_absmax walks, and the most it takes: its walk steps past
+// the last block by up to a grid in 32-bit integers.
+long long absmax_blocks(const K1Args& a, wino_layout layout, const int8_t* x) {
+    const int tx = k1_direct(a, layout, x) ? 8 : K1_TX;
+    return (long long)((a.tw + tx - 1) / tx) * a.ncg * a.n * a.th;
+}
+constexpr long long kAbsmaxMaxBlocks = 0x7fffffffll - kAbsmaxGroups;
+
 // Per-tap maxima of |V| over the input into out[ntap]; scratch: kAbsmaxGroups x
-// ntap int32.  Inputs that the direct kernel does not take go through the band.
+// ntap int32; at most kAbsmaxMaxBlocks blocks.  Inputs that the direct kernel does
+// not take go through the band.
 template <int M>
 wino_status launch_absmax(const K1Args& a, wino_layout layout, const int8_t* x, int* out, int* scratch,
                           hipStream_t stream) {
@@ -1473,13 +1482,11 @@ wino_status launch_absmax(const K1Args& a, wino_layout layout, const int8_t* x, 
     int groups;
     if (k1_direct(a, layout, x)) {
         args = k1_blocks<8>(a, layout, x, blocks);
-        if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
         groups = (int)std::min<long long>(blocks, kAbsmaxGroups);
         hipLaunchKernelGGL((wino_input_absmax<M, WINO_NHWC, 8>), dim3(groups), dim3(128), 0, stream, x, scratch,
                            (int)blocks, args);
     } else {
         args = k1_blocks<K1_TX>(a, layout, x, blocks);
-        if (blocks > 0x7fffffffll) return WINO_EUNSUPPORTED;
         groups = (int)std::min<long long>(blocks, kAbsmaxGroups);
         if (layout == WINO_NCHW)
             hipLaunchKernelGGL((wino_input_absmax<M, WINO_NCHW, K1_TX>), dim3(groups), dim3(16 * K1_TX), 0, stream, x,
@@ -2110,10 +2117,11 @@ static wino_status calibrate_input(int m, int bits, const int8_t* x, int32_t n, 
     const int ntap = (m + 2) * (m + 2);
     int host[kTaps] = {0};
     if (g.ntiles > 0) {
-        int* dmax = nullptr;
-        if (hipMalloc(&dmax, sizeof(int) * kTaps * (1 + kAbsmaxGroups)) != hipSuccess) return WINO_ENOMEM;
         TapTables tab = {};
         const K1Args a = k1_args(g, cin, (int)round_up(cin, kKStep), tab);
+        if (absmax_blocks(a, layout, x) > kAbsmaxMaxBlocks) return WINO_EUNSUPPORTED;
+        int* dmax = nullptr;
+        if (hipMalloc(&dmax, sizeof(int) * kTaps * (1 + kAbsmaxGroups)) != hipSuccess) return WINO_ENOMEM;
         bool ok = (m == 2 ? launch_absmax<2>(a, layout, x, dmax, dmax + kTaps, stream)
                           : launch_absmax<4>(a, layout, x, dmax, dmax + kTaps, stream)) == WINO_OK;
         if (ok) ok = hipMemcpyAsync(host, dmax, sizeof(int) * kTaps, hipMemcpyDeviceToHost, stream) == hipSuccess;

@@ -214,6 +214,20 @@ def test_invalid_arguments_return_status():
     assert W.wino_strerror(-5).startswith("workspace")
 
 
+def test_calibration_block_limit():
+    """Input calibration walks its blocks in 32-bit steps of up to 1024; more
+    than 2^31 - 1 - 1024 of them (here one-tile images of 32 channel groups) are
+    refused before any device work, like sizes past the tile limit."""
+    lib = _lib()
+    x = np.zeros(16, np.int8)
+    addr = (x.ctypes.data + 15) // 16 * 16      # never read
+    for layout in (W.NCHW, W.NHWC):
+        for fn in (lib.wino_f4_calibrate_input, lib.wino_f2_calibrate_input, lib.wino_f4_calibrate_input_i10):
+            assert fn(addr, 2 ** 26 - 1, 2048, 1, 1, layout, None, None, None) == -2
+            assert fn(addr, 2 ** 26 - 32, 2048, 1, 1, layout, None, None, None) == -2
+            assert fn(addr, 2 ** 26, 1, 1, 1, layout, None, None, None) == -2
+
+
 def test_epilogue_width_decision():
     """The host bound picks 32 bits for calibrated data and 64 bits when the
     alignment shifts are large, as the oracle's bound says."""
