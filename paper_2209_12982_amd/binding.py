@@ -32,8 +32,8 @@ EXPORTS = [
     "wino_f4_debug_input_transform", "wino_f4_debug_tap_gemm",
     "direct_conv_quantize_weights", "direct_conv_int8", "wino_f4_conv_float", "wino_strerror",
 ]
-# include/winof4_probe.h: the measurement probe, outside the method's interface.
-PROBE_EXPORTS = ["wino_probe_mfma_int8"]
+# include/winof4_probe.h: the measurement probes, outside the method's interface.
+PROBE_EXPORTS = ["wino_probe_mfma_int8", "wino_probe_conv_kernels"]
 
 
 class LibraryNotBuilt(RuntimeError):
@@ -103,6 +103,7 @@ def load_library():
         "direct_conv_int8": (I32, [P, P, P, P, I32, I32, I32, I32, I32, I32, I32, I32, P]),
         "wino_f4_conv_float": (I32, [P, P, P, I32, I32, I32, I32, I32, I32, P]),
         "wino_probe_mfma_int8": (I32, [I32, I32, I32, P, P, P]),
+        "wino_probe_conv_kernels": (I32, [P, P, I32, I32, I32, I32, P]),
         "wino_strerror": (ctypes.c_char_p, [I32]),
     }
     for name, (res, args) in sig.items():
@@ -546,3 +547,22 @@ def wino_probe_mfma_int8(shape, iters, blocks, sink, stream=None):
                                              ctypes.byref(ops), _stream(stream))
     _check(st, "wino_probe_mfma_int8")
     return ops.value
+
+
+class _ProbeKernels(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("launches", "xform", "xform_tiles", "gemm", "co", "tiles")]
+
+
+PROBE_XFORMS = {0: None, 1: "direct", 2: "band"}
+PROBE_GEMMS = {0: None, 1: "small", 2: "resident", 3: "rows", 4: "rows_streamk", 5: "waves", 6: "rows_wide"}
+
+
+def wino_probe_conv_kernels(plan, x, n, h, w, layout=NCHW):
+    """Which kernels a SPLIT wino_f4_conv_int8 launches for input x (a tensor or
+    an address): a dict of launches, xform, xform_tiles, gemm, co, tiles."""
+    k = _ProbeKernels()
+    addr = x if isinstance(x, int) else x.data_ptr()
+    _check(load_library().wino_probe_conv_kernels(plan.handle, addr, int(n), int(h), int(w), int(layout),
+                                                  ctypes.byref(k)), "wino_probe_conv_kernels")
+    d = {f: getattr(k, f) for f, _ in k._fields_}
+    return dict(d, xform=PROBE_XFORMS[d["xform"]], gemm=PROBE_GEMMS[d["gemm"]])

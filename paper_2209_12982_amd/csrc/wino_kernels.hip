@@ -31,6 +31,7 @@
 #include <atomic>
 #include <mutex>
 #include "wino_device.h"
+#include "winof4_probe.h"
 
 using namespace winof4;
 
@@ -1449,16 +1450,20 @@ wino_status launch_k1_band(const K1Args& a, const int8_t* x, int8_t* vq, hipStre
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
+// tiles per block of the band transform.  NCHW: 8 where that leaves fewer idle
+// tiles in a row; on a tie 16, whose band has the smaller share of halo columns
+// (1x64x568x568, rows of 142 tiles: 17.9 us against 20.8)
+int k1_band_tx(int tw, wino_layout layout) {
+    return layout == WINO_NCHW && (tw + 7) / 8 * 8 < (tw + 15) / 16 * 16 ? 8 : K1_TX;
+}
+
 template <int M, int Q>
 wino_status launch_k1(const K1Args& a, wino_layout layout, const int8_t* x, int8_t* vq, hipStream_t stream) {
     if (k1_direct(a, layout, x))
         return k1_direct_tx(a.tw) == 8 ? launch_k1_direct<M, Q, 8>(a, layout, x, vq, stream)
                                        : launch_k1_direct<M, Q, 16>(a, layout, x, vq, stream);
     if (layout == WINO_NHWC) return launch_k1_band<M, WINO_NHWC, Q, K1_TX>(a, x, vq, stream);
-    // NCHW: 8 tiles per block where that leaves fewer idle tiles in a row; on a
-    // tie 16, whose band has the smaller share of halo columns (1x64x568x568, rows
-    // of 142 tiles: 17.9 us against 20.8)
-    if ((a.tw + 7) / 8 * 8 < (a.tw + 15) / 16 * 16) return launch_k1_band<M, WINO_NCHW, Q, 8>(a, x, vq, stream);
+    if (k1_band_tx(a.tw, layout) == 8) return launch_k1_band<M, WINO_NCHW, Q, 8>(a, x, vq, stream);
     return launch_k1_band<M, WINO_NCHW, Q, K1_TX>(a, x, vq, stream);
 }
 
@@ -1711,6 +1716,16 @@ wino_status launch_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout
 // 8.7 [64] 6.7 [128] 5.6 [256]; 256->512 13.8 [256] 18.3 [512] 21.9 [1024]; F4
 // 2x75x75 256->256 16.1 [184] 20.2 [368] 17.9 [736]; F2 8x14x14 256->256 7.8
 // [104] 6.2 [208] 6.7 [400]; F2 8x56x56 64->64 5.7 [392] 5.6 [784] 6.6 [1568]).
+struct SmallShape {
+    int cb, tb;                          // sixteens of channels and tiles
+};
+SmallShape small_shape(const wino_f4_plan_s* p, const Geometry& g) {
+    const long long want = (long long)num_cus() * 5 / 8, t32 = (g.ntiles + 31) / 32;
+    if (t32 * ((p->cout + 31) / 32) >= want) return {2, 2};
+    if (t32 * ((p->cout + 15) / 16) >= want) return {1, 2};
+    return {1, 1};
+}
+
 // F2 from 256 input channels on, where 32x32 blocks need more than one round of the
 // compute units and the tap-resident kernel's 64x32 blocks do not, keeps the latter
 // (8x256->512 20x20: 14.0 against 16.8 us for the layer, 4x256->256 40x40: 14.5
@@ -1721,13 +1736,19 @@ bool f2_wide_blocks(const wino_f4_plan_s* p, const Geometry& g) {
     return p->cin_pad >= 4 * kKStep && t32 * ((p->cout + 31) / 32) > cus && t32 * (p->cout_pad / 64) <= cus;
 }
 
+// whether the tap GEMM of a convolution (or its output maximum) is
+// wino_tap_gemm_small: 8-bit, 32-bit epilogue, under AUTO
+bool small_kernel(const wino_f4_plan_s* p, const Geometry& g) {
+    if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return false;
+    return p->m == 2 ? !f2_wide_blocks(p, g) : tap_kernel_for(p, g, 0) != WINO_TAP_ROWS;
+}
+
 template <int M, int MODE>
 wino_status launch_small_auto(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* vq,
                               int8_t* y, void* aux, const K2Args& a, hipStream_t stream) {
-    const long long want = (long long)num_cus() * 5 / 8;
-    const long long t32 = (g.ntiles + 31) / 32;
-    if (t32 * ((p->cout + 31) / 32) >= want) return launch_small<M, 2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
-    if (t32 * ((p->cout + 15) / 16) >= want) return launch_small<M, 1, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
+    const SmallShape b = small_shape(p, g);
+    if (b.cb == 2) return launch_small<M, 2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
+    if (b.tb == 2) return launch_small<M, 1, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
     return launch_small<M, 1, 1, MODE>(p, g, layout, vq, y, aux, a, stream);
 }
 
@@ -1787,14 +1808,11 @@ wino_status launch_k2(const wino_f4_plan_s* p, const Geometry& g, wino_layout la
     // AUTO with the 32-bit epilogue, a convolution or its output maximum: F4 from
     // the row-streamed kernel's sizes on, and the small-layer kernel
     if constexpr (MODE <= 1) {
-        if (p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO) {
-            if (p->m == 2 && !f2_wide_blocks(p, g))
-                return launch_small_auto<2, MODE>(p, g, layout, vq, y, aux, a, stream);
-            if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
-            if (tap_kernel_for(p, g, 0) != WINO_TAP_ROWS)
-                return launch_small_auto<4, MODE>(p, g, layout, vq, y, aux, a, stream);
+        if (small_kernel(p, g))
+            return p->m == 2 ? launch_small_auto<2, MODE>(p, g, layout, vq, y, aux, a, stream)
+                             : launch_small_auto<4, MODE>(p, g, layout, vq, y, aux, a, stream);
+        if (p->m == 4 && p->epi_bits == 32 && p->tap_kernel == WINO_TAP_AUTO)
             return launch_rows_auto<MODE>(p, g, layout, vq, y, aux, a, stream);
-        }
     }
     if (p->m == 2) return launch_resident<K2F2, 2, MODE>(p, g, layout, vq, y, aux, a, stream);
     switch (tap_kernel_for(p, g, MODE)) {
@@ -1905,7 +1923,7 @@ wino_status launch_conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_l
 }
 
 // The convolution in one launch (wino_conv_small) where that is faster than the
-// input transform and the small tap GEMM; false: not taken.  The block takes the
+// input transform and the small tap GEMM.  The block takes the
 // most channels (64, 32, 16) that leave 5/8 of the compute units a block.  The
 // limits: every block of output channels repeats the transform, and a block
 // walks its 64-channel chunks one after another (us of kernel time, one launch
@@ -1913,26 +1931,27 @@ wino_status launch_conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_l
 // 8x256->256 14x14 9.1 / 10.6, 8x128->256 28x28 10.6 / 12.4, 8x64->128 56x56 13.3 /
 // 14.1; F4 1x64->64 28x28 7.8 / 9.3, 8x128->128 32x32 10.7 / 10.7, and one launch
 // less; 1x240->64 21x27 15.6 / 12.1).  F4's larger blocks lose to 16 x 16.
-bool conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,
-                hipStream_t stream, wino_status& st) {
-    if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return false;
+// Returns the block's channels in sixteens, 0: not taken.
+int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x) {
+    if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return 0;
     const long long xb = (long long)g.n * g.h * g.w * p->cin;
-    if (xb >= 0x7ffffff0ll || (layout == WINO_NHWC ? p->cin < 4 : g.w < 4) || ((uintptr_t)x & 3) != 0) return false;
+    if (xb >= 0x7ffffff0ll || (layout == WINO_NHWC ? p->cin < 4 : g.w < 4) || ((uintptr_t)x & 3) != 0) return 0;
     const long long cus = num_cus(), tb = (g.ntiles + 15) / 16;
     const int nkc = p->cin_pad / kKStep;
     auto blocks = [&](int cb) { return tb * ((p->cout + 16 * cb - 1) / (16 * cb)); };
-    int cb = 1;
-    if (p->m == 2) {
-        if (blocks(4) >= cus * 5 / 8) cb = 4;
-        else if (blocks(2) >= cus * 5 / 8) cb = 2;
-        if (blocks(cb) * nkc > 4 * cus) return false;
-    } else if (nkc > 2 || blocks(1) > cus) {
-        return false;
-    }
+    if (p->m == 4) return nkc > 2 || blocks(1) > cus ? 0 : 1;
+    const int cb = blocks(4) >= cus * 5 / 8 ? 4 : blocks(2) >= cus * 5 / 8 ? 2 : 1;
+    return blocks(cb) * nkc > 4 * cus ? 0 : cb;
+}
+
+bool conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,
+                hipStream_t stream, wino_status& st) {
+    const int cb = one_launch_cb(p, g, layout, x);
+    if (cb == 0) return false;
     CsArgs a;
     a.k = k2_args(p, g, layout, y);
     a.cin = p->cin;
-    a.x_bytes = (int)xb;
+    a.x_bytes = (int)((long long)g.n * g.h * g.w * p->cin);
     const K1Args k1 = k1_args(g, p->cin, p->cin_pad, a.k.tab);
     a.q_sat = k1.q_sat;
     for (int t = 0; t < kTaps; ++t) a.rnd2[t] = k1.rnd2[t];
@@ -2060,6 +2079,47 @@ wino_status scratch_for_device(int dev, void** out) {
     return WINO_OK;
 }
 }  // namespace
+
+// The kernels that a SPLIT wino_f4_conv_int8 launches, from the functions that
+// the launches themselves ask.
+extern "C" wino_status wino_probe_conv_kernels(wino_f4_plan_t p, const int8_t* x, int32_t n, int32_t h, int32_t w,
+                                               wino_layout layout, wino_probe_kernels* k) {
+    if (!p || !k || (layout != WINO_NCHW && layout != WINO_NHWC)) return WINO_EINVAL;
+    Geometry g;
+    const wino_status st = geometry(n, h, w, p->m, g);
+    if (st != WINO_OK) return st;
+    *k = {};
+    if (g.ntiles == 0) return WINO_OK;
+    if (const int cb = one_launch_cb(p, g, layout, x)) {
+        *k = {1, WINO_PROBE_XFORM_NONE, 0, WINO_PROBE_GEMM_SMALL, 16 * cb, 16};
+        return WINO_OK;
+    }
+    const K1Args a = k1_args(g, p->cin, p->cin_pad, tables_of(p), p->bits);
+    const bool direct = k1_direct(a, layout, x);
+    k->launches = 2;
+    k->xform = direct ? WINO_PROBE_XFORM_DIRECT : WINO_PROBE_XFORM_BAND;
+    k->xform_tiles = direct ? k1_direct_tx(a.tw) : k1_band_tx(a.tw, layout);
+    auto gemm = [&](int kind, int co, int tiles) { k->gemm = kind; k->co = co; k->tiles = tiles; };
+    if (small_kernel(p, g)) {
+        const SmallShape b = small_shape(p, g);
+        gemm(WINO_PROBE_GEMM_SMALL, 16 * b.cb, 16 * b.tb);
+        return WINO_OK;
+    }
+    SkPlan sk;
+    switch (tap_kernel_for(p, g, 0)) {
+        case WINO_TAP_ROWS:
+            if (p->bits == 10) gemm(WINO_PROBE_GEMM_ROWS_WIDE, KW_CO, KW_TL);
+            else if (sk_plan_for(p, g, sk)) gemm(WINO_PROBE_GEMM_ROWS_STREAMK, KR_CO, KR_TL);
+            else gemm(WINO_PROBE_GEMM_ROWS, RW_CO, p->cin_pad == kKStep ? RwNarrow::TL : RwWide::TL);
+            break;
+        case WINO_TAP_WAVES: gemm(WINO_PROBE_GEMM_WAVES, WS_CO, WS_TL); break;
+        case WINO_TAP_RESIDENT_32X32: gemm(WINO_PROBE_GEMM_RESIDENT, K2Mid::CO, K2Mid::TL); break;
+        case WINO_TAP_RESIDENT_16X16: gemm(WINO_PROBE_GEMM_RESIDENT, p->bits == 10 ? K2Small10::CO : K2Small::CO,
+                                           p->bits == 10 ? K2Small10::TL : K2Small::TL); break;
+        default: gemm(WINO_PROBE_GEMM_RESIDENT, K2Big::CO, K2Big::TL); break;
+    }
+    return WINO_OK;
+}
 
 extern "C" wino_status wino_f4_conv_int8_noalloc(wino_f4_plan_t p, const int8_t* x, int8_t* y, int32_t n,
                                                  int32_t h, int32_t w, wino_layout layout, hipStream_t stream) {
