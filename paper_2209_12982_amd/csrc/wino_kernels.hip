@@ -1450,11 +1450,19 @@ wino_status launch_k1_band(const K1Args& a, const int8_t* x, int8_t* vq, hipStre
     return hipGetLastError() == hipSuccess ? WINO_OK : WINO_EHIP;
 }
 
-// tiles per block of the band transform.  NCHW: 8 where that leaves fewer idle
-// tiles in a row; on a tie 16, whose band has the smaller share of halo columns
-// (1x64x568x568, rows of 142 tiles: 17.9 us against 20.8)
-int k1_band_tx(int tw, wino_layout layout) {
-    return layout == WINO_NCHW && (tw + 7) / 8 * 8 < (tw + 15) / 16 * 16 ? 8 : K1_TX;
+// Tiles per block of the band transform.  NCHW: 8 where 16 would run over a fifth
+// more tiles in a row, else 16.  An 8-tile band reads rows in shorter pieces, half
+// as many bytes of a line each, and has the larger share of halo columns (us, 8 / 16
+// tiles, tiles run in brackets.  F4: 8x512x33x66 [24 : 32] 12.1 / 14.1, 8x64x139x80
+// 8.4 / 9.9; 8x64x283x208 [56 : 64] 26.4 / 23.8, 8x512x150x195 172 / 148,
+// 4x128x408x392 [104 : 112] 65.3 / 53.5.  F2: 1x64x343x204 [104 : 112] 10.2 / 8.5,
+// 8x128x189x208 50.7 / 40.4).  At a fifth exactly ([40 : 48]) F4 takes 8 below 8 MB
+// of input (2x128x183x144 9.2 / 10.2, 8x512x196x136 145 / 123).
+int k1_band_tx(const K1Args& a, int m, wino_layout layout) {
+    const int run8 = (a.tw + 7) / 8 * 8, run16 = (a.tw + 15) / 16 * 16;
+    if (layout != WINO_NCHW || 5 * run16 < 6 * run8) return K1_TX;
+    const bool small = m == 4 && (long long)a.n * a.cin * a.h * a.w < 8000000;
+    return 5 * run16 > 6 * run8 || small ? 8 : K1_TX;
 }
 
 template <int M, int Q>
@@ -1463,7 +1471,7 @@ wino_status launch_k1(const K1Args& a, wino_layout layout, const int8_t* x, int8
         return k1_direct_tx(a.tw) == 8 ? launch_k1_direct<M, Q, 8>(a, layout, x, vq, stream)
                                        : launch_k1_direct<M, Q, 16>(a, layout, x, vq, stream);
     if (layout == WINO_NHWC) return launch_k1_band<M, WINO_NHWC, Q, K1_TX>(a, x, vq, stream);
-    if (k1_band_tx(a.tw, layout) == 8) return launch_k1_band<M, WINO_NCHW, Q, 8>(a, x, vq, stream);
+    if (k1_band_tx(a, M, layout) == 8) return launch_k1_band<M, WINO_NCHW, Q, 8>(a, x, vq, stream);
     return launch_k1_band<M, WINO_NCHW, Q, K1_TX>(a, x, vq, stream);
 }
 
@@ -2098,7 +2106,7 @@ extern "C" wino_status wino_probe_conv_kernels(wino_f4_plan_t p, const int8_t* x
     const bool direct = k1_direct(a, layout, x);
     k->launches = 2;
     k->xform = direct ? WINO_PROBE_XFORM_DIRECT : WINO_PROBE_XFORM_BAND;
-    k->xform_tiles = direct ? k1_direct_tx(a.tw) : k1_band_tx(a.tw, layout);
+    k->xform_tiles = direct ? k1_direct_tx(a.tw) : k1_band_tx(a, p->m, layout);
     auto gemm = [&](int kind, int co, int tiles) { k->gemm = kind; k->co = co; k->tiles = tiles; };
     if (small_kernel(p, g)) {
         const SmallShape b = small_shape(p, g);
