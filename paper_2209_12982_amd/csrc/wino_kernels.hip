@@ -1931,14 +1931,22 @@ wino_status launch_conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_l
 }
 
 // The convolution in one launch (wino_conv_small) where that is faster than the
-// input transform and the small tap GEMM.  The block takes the
-// most channels (64, 32, 16) that leave 5/8 of the compute units a block.  The
-// limits: every block of output channels repeats the transform, and a block
-// walks its 64-channel chunks one after another (us of kernel time, one launch
-// against the two: F2 1x16->16 32x32 NCHW 6.3 / 7.6, 8x64->64 56x56 8.4 / 11.0,
-// 8x256->256 14x14 9.1 / 10.6, 8x128->256 28x28 10.6 / 12.4, 8x64->128 56x56 13.3 /
-// 14.1; F4 1x64->64 28x28 7.8 / 9.3, 8x128->128 32x32 10.7 / 10.7, and one launch
-// less; 1x240->64 21x27 15.6 / 12.1).  F4's larger blocks lose to 16 x 16.
+// input transform and the small tap GEMM.  The block takes the most channels (64,
+// 32, 16) that leave 5/8 of the compute units a block; F4's larger blocks lose to
+// 16 x 16.  The limits: every block of output channels repeats the transform, a
+// block walks its 64-channel chunks one after another, and in NCHW, where a chunk's
+// words come from 64 channel planes, a chunk costs about twice as much.  us per
+// call, one launch against the two (b: blocks per compute unit):
+//   NHWC F2, 16-channel blocks: 1 chunk 7.0 / 9.7, 4 8.5 / 9.7, 5 9.5 / 9.7, 6 10.5 /
+//   9.7, 8 12.4 / 10.3; 64-channel ones: 8x64->64 56x56 8.4 / 11.0, 8x128->256 28x28
+//   10.6 / 12.4, 2x384->384 25x33 (6 chunks) 12.8 / 14.6.  F4: 1 chunk 7.8 / 9.9, 2
+//   10.1 / 10.0 and one launch less; 1x240->64 21x27 (4) 15.6 / 12.1.
+//   NCHW F2: 1 chunk 7.0 / 9.7, b > 2: 1x64->384 94x64 15.4 / 11.1, 4x64->512 37x51
+//   17.7 / 14.0, a single channel block 1x32->32 196x249 (b 3) 12.4 / 13.3; 2 chunks
+//   8.2 / 9.7, b > 1: 1x128->128 96x132 15.7 / 13.9, 4x128->64 64x80 (b 1.25) 15.6 /
+//   14.2, a single channel block from b 1.5 on 1x96->64 169x163 12.8 / 16.6; 3 chunks
+//   10.0 / 9.7, 2x192->192 42x36 18.1 / 11.7; 8 chunks 20.3 / 11.1.  F4: 1 chunk
+//   10.0 / 10.8, 2 15.3 / 11.8.
 // Returns the block's channels in sixteens, 0: not taken.
 int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x) {
     if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return 0;
@@ -1946,10 +1954,19 @@ int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout
     if (xb >= 0x7ffffff0ll || (layout == WINO_NHWC ? p->cin < 4 : g.w < 4) || ((uintptr_t)x & 3) != 0) return 0;
     const long long cus = num_cus(), tb = (g.ntiles + 15) / 16;
     const int nkc = p->cin_pad / kKStep;
-    auto blocks = [&](int cb) { return tb * ((p->cout + 16 * cb - 1) / (16 * cb)); };
-    if (p->m == 4) return nkc > 2 || blocks(1) > cus ? 0 : 1;
+    auto nco = [&](int cb) { return (p->cout + 16 * cb - 1) / (16 * cb); };
+    auto blocks = [&](int cb) { return tb * nco(cb); };
+    if (p->m == 4) return nkc > (layout == WINO_NHWC ? 2 : 1) || blocks(1) > cus ? 0 : 1;
     const int cb = blocks(4) >= cus * 5 / 8 ? 4 : blocks(2) >= cus * 5 / 8 ? 2 : 1;
-    return blocks(cb) * nkc > 4 * cus ? 0 : cb;
+    const long long nb = blocks(cb);
+    bool take;
+    if (layout == WINO_NHWC)
+        take = nb * nkc <= 4 * cus && (nkc <= 5 || cb == 4);
+    else if (nkc == 1)
+        take = nb <= (nco(cb) == 1 ? 3 : 2) * cus;
+    else
+        take = nkc == 2 && (nb <= cus || (nco(cb) == 1 && 2 * nb >= 3 * cus && nb <= 2 * cus));
+    return take ? cb : 0;
 }
 
 bool conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,

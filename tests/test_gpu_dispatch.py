@@ -37,3 +37,19 @@ def _kernels(m, n, cin, cout, h, w, layout, epi=32):
 def test_band_transform_width(m, n, cin, h, w, tiles):
     k = _kernels(m, n, cin, 512, h, w, W.NCHW, epi=None)
     assert (k["launches"], k["xform"], k["xform_tiles"]) == (2, "band", tiles), k
+
+
+# The one launch, 0 for two launches, else its block's channels
+@pytest.mark.parametrize("m,layout,n,cin,cout,h,w,co", [
+    (2, W.NCHW, 1, 16, 16, 32, 32, 16), (2, W.NCHW, 8, 64, 64, 56, 56, 64),
+    (2, W.NCHW, 1, 64, 384, 94, 64, 0), (2, W.NCHW, 8, 64, 512, 28, 28, 0), (2, W.NCHW, 1, 32, 32, 196, 249, 64),
+    (2, W.NCHW, 1, 128, 128, 47, 39, 16), (2, W.NCHW, 1, 128, 128, 112, 112, 0), (2, W.NCHW, 4, 128, 64, 64, 80, 0),
+    (2, W.NCHW, 1, 96, 64, 169, 163, 64), (2, W.NCHW, 2, 192, 192, 42, 36, 0), (2, W.NCHW, 1, 512, 64, 28, 28, 0),
+    (2, W.NHWC, 8, 64, 64, 56, 56, 64), (2, W.NHWC, 8, 256, 256, 14, 14, 32), (2, W.NHWC, 1, 320, 64, 14, 14, 16),
+    (2, W.NHWC, 2, 384, 384, 25, 33, 64), (2, W.NHWC, 1, 384, 64, 14, 14, 0), (2, W.NHWC, 1, 512, 64, 14, 14, 0),
+    (4, W.NHWC, 8, 128, 128, 32, 32, 16), (4, W.NHWC, 1, 192, 64, 28, 28, 0),
+    (4, W.NCHW, 1, 64, 64, 28, 28, 16), (4, W.NCHW, 8, 128, 128, 32, 32, 0), (4, W.NCHW, 1, 96, 64, 28, 28, 0),
+])
+def test_one_launch(m, layout, n, cin, cout, h, w, co):
+    k = _kernels(m, n, cin, cout, h, w, layout)
+    assert (k["co"] if k["launches"] == 1 else 0) == co, k
