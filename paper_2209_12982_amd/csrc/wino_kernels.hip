@@ -1734,14 +1734,30 @@ SmallShape small_shape(const wino_f4_plan_s* p, const Geometry& g) {
     return {1, 1};
 }
 
-// F2 from 256 input channels on, where 32x32 blocks need more than one round of the
-// compute units and the tap-resident kernel's 64x32 blocks do not, keeps the latter
-// (8x256->512 20x20: 14.0 against 16.8 us for the layer, 4x256->256 40x40: 14.5
-// against 15.4; with fewer channels, or more or fewer blocks, the small-layer
-// kernel is ahead).
+// F2 layers that keep the tap-resident kernel's 64 x 32 blocks, for one of two
+// reasons (us of the layer, 64 x 32 / small-layer kernel).
+// Rounds: a compute unit runs one 64 x 32 block at a time (144 KB of LDS) and two
+// of the 32 x 32 ones, which halve the work but share no operand through LDS.
+// Where the 32 x 32 blocks give some compute unit twice as many as the 64 x 32
+// ones, nothing is saved and the operands are read more often: one 64 x 32 block
+// each, 2 chunks 1x128->384 74x61 11.8 / 13.2, 3 2x192->320 52x46 12.6 / 16.9, 4
+// 8x256->512 20x19 14.1 / 17.2 (1 chunk 1x64->384 63x57 11.1 / 9.8); two each, only
+// from 5 chunks and 3 blocks of channels on, 8x512->512 25x33 36.3 / 38.5 (4 chunks
+// 1x256->256 126x112 24.4 / 25.4, 8 and 128 channels 47.8 / 45.8).  In between the
+// small-layer kernel is ahead (1.25 rounds, 1x384->512 27.6 / 23.7).
+// Distance: once Vq outgrows the last-level cache (256 MB) the 64 x 32 kernel, a
+// 12-tap stage ahead, takes the longer latency better and reads Vq once per 64
+// channels: 4x320->48 173x249 (223 MB) 120 / 139, 1x512->256 401x336 (277 MB) 322 /
+// 377, 2x192->64 487x360 (270 MB) 160 / 187; below, 8x256->64 175x125 (182 MB) 89 /
+// 79; with 2 chunks 8x128->128 309x210 (267 MB) 286 / 266; with half of the 64
+// channels idle 4x128->32 310x433 (276 MB) 176 / 157.
 bool f2_wide_blocks(const wino_f4_plan_s* p, const Geometry& g) {
     const long long cus = num_cus(), t32 = (g.ntiles + 31) / 32;
-    return p->cin_pad >= 4 * kKStep && t32 * ((p->cout + 31) / 32) > cus && t32 * (p->cout_pad / 64) <= cus;
+    const long long nco32 = (p->cout + 31) / 32, nco64 = p->cout_pad / 64;
+    const int nkc = p->cin_pad / kKStep;
+    if (nkc >= 2 && t32 * nco32 > cus && t32 * nco64 <= cus) return true;
+    if (nkc >= 5 && nco64 >= 3 && t32 * nco32 > 3 * cus && t32 * nco64 <= 2 * cus) return true;
+    return nkc >= 3 && nco32 == 2 * nco64 && vq_bytes(p, g) >= (208u << 20);
 }
 
 // whether the tap GEMM of a convolution (or its output maximum) is

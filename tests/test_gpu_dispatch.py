@@ -53,3 +53,19 @@ def test_band_transform_width(m, n, cin, h, w, tiles):
 def test_one_launch(m, layout, n, cin, cout, h, w, co):
     k = _kernels(m, n, cin, cout, h, w, layout)
     assert (k["co"] if k["launches"] == 1 else 0) == co, k
+
+
+# F2 tap GEMM of two launches: the tap-resident kernel's 64 x 32 blocks or the
+# small-layer kernel
+@pytest.mark.parametrize("n,cin,cout,h,w,gemm", [
+    (2, 192, 320, 52, 46, "resident"), (8, 192, 384, 20, 28, "resident"), (1, 256, 128, 118, 90, "resident"),
+    (1, 192, 192, 85, 85, "resident"), (1, 64, 512, 112, 112, "small"), (1, 256, 256, 112, 112, "small"),
+    (8, 512, 512, 25, 33, "resident"), (1, 320, 384, 96, 96, "resident"), (1, 256, 256, 126, 112, "small"),
+    (1, 512, 128, 198, 140, "small"), (1, 512, 512, 64, 80, "small"),
+    (4, 320, 48, 173, 249, "resident"), (2, 192, 64, 487, 360, "resident"), (8, 256, 64, 175, 125, "small"),
+    (8, 128, 128, 309, 210, "small"), (4, 256, 32, 310, 433, "small"),
+])
+def test_f2_tap_gemm(n, cin, cout, h, w, gemm):
+    for layout in (W.NCHW, W.NHWC):
+        k = _kernels(2, n, cin, cout, h, w, layout, epi=None if cin > 256 else 32)
+        assert (k["launches"], k["gemm"]) == (2, gemm), k
