@@ -70,10 +70,11 @@ typedef struct wino_f4_plan_s* wino_f4_plan_t;   /* opaque, immutable after crea
  * 64 x 64 blocks.  WAVES (F4, 8-bit, 32-bit epilogue; forced only) splits a
  * 64 x 64 block between four 32x32x32-MFMA waves and eight waves that copy
  * operands and keep the output rows, persistent over the blocks.  AUTO picks
- * ROWS when its blocks fill a third of the device and the 32-bit epilogue
- * applies; else, reported as RESIDENT_64X32, the tap-resident kernels: with the
- * 32-bit epilogue one that spreads a small block's taps over its waves, with
- * the 64-bit one the 64 x 32 shape.  ROWS_STREAMK (forced only: measured slower than ROWS)
+ * ROWS when the output makes more 32 x 32 blocks than the device has compute
+ * units and the 32-bit epilogue applies; else, reported as RESIDENT_64X32, the
+ * tap-resident kernels: with the 32-bit epilogue one that spreads a small
+ * block's taps over its waves (F2: that one or the 64 x 32 shape, by measured
+ * limits), with the 64-bit one the 64 x 32 shape.  ROWS_STREAMK (forced only: measured slower than ROWS)
  * is ROWS with the blocks of its last, partial round of workgroups split by
  * stages over every compute unit (stream-K): each workgroup runs an equal
  * share of those blocks' stages, leaves partial sums in the workspace and the

@@ -1520,14 +1520,16 @@ long long resident_blocks(const wino_f4_plan_s* p, const Geometry& g) {
 
 // The tap-GEMM kernel of a convolution (a wino_tap_kernel value other than
 // AUTO and RESIDENT).  The row-streamed kernel needs the 32-bit epilogue and
-// an output convolution; AUTO takes it from a third of the device's compute
-// units in 64x64 blocks on, below which wino_tap_gemm_small is faster (us, rows
-// against small: 144 blocks, 256 channels 19.9 / 35.2; 144 blocks, 128 channels
-// 14.0 / 24.3; 157 blocks, 64 channels 12.2 / 18.5; 64 blocks, 128 channels
-// 13.5 / 9.7; 64 blocks, 256 channels 19.5 / 13.8).  RESIDENT_64X32 under AUTO
-// stands for the kernels that keep all taps: wino_tap_gemm_small with the 32-bit
-// epilogue, else the 64x32 shape.  Debug exports (MODE 2), and calibration
-// (MODE 1) of a plan with a forced kernel, use the 64x32 shape.
+// an output convolution; AUTO takes it once wino_tap_gemm_small's 32 x 32 blocks
+// (108 KB of LDS: one per compute unit) need a second round (us of the layer, NHWC,
+// rows / small, 32 x 32 blocks in brackets: 1x64->256 116x109 [208] 13.1 / 12.7,
+// 1x256->256 129x124 [256] 23.6 / 19.1, 4x256->32 150x202 [243] 38.8 / 33.2;
+// 2x64->256 76x120 [288] 12.9 / 17.2, 1x128->256 131x127 [264] 17.9 / 21.8,
+// 8x256->128 95x64 [384] 27.1 / 33.0, 1x256->32 467x300 [275] 41.0 / 45.4).
+// RESIDENT_64X32 under AUTO stands for the kernels that keep all taps:
+// wino_tap_gemm_small with the 32-bit epilogue, else the 64x32 shape.  Debug
+// exports (MODE 2), and calibration (MODE 1) of a plan with a forced kernel, use
+// the 64x32 shape.
 int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     const int k = p->tap_kernel;
     // int8/10 (fp16 operands): the row-streamed 64x32 kernel by default; a
@@ -1554,7 +1556,7 @@ int tap_kernel_for(const wino_f4_plan_s* p, const Geometry& g, int mode) {
     }
     if (p->epi_bits == 32 && k != WINO_TAP_RESIDENT &&
         (k == WINO_TAP_ROWS || k == WINO_TAP_ROWS_STREAMK ||
-         (long long)(p->cout_pad / KR_CO) * (g.t_pad / KR_TL) * 3 >= num_cus()))
+         (g.ntiles + 31) / 32 * ((p->cout + 31) / 32) > num_cus()))
         return WINO_TAP_ROWS;
     return WINO_TAP_RESIDENT_64X32;
 }

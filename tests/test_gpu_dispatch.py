@@ -69,3 +69,33 @@ def test_f2_tap_gemm(n, cin, cout, h, w, gemm):
     for layout in (W.NCHW, W.NHWC):
         k = _kernels(2, n, cin, cout, h, w, layout, epi=None if cin > 256 else 32)
         assert (k["launches"], k["gemm"]) == (2, gemm), k
+
+
+# F4 tap GEMM of two launches: the small-layer kernel while its 32 x 32 blocks run
+# at once, then the row-streamed one
+@pytest.mark.parametrize("n,cin,cout,h,w,gemm", [
+    (1, 96, 320, 134, 118, "rows"), (2, 64, 256, 76, 120, "rows"), (1, 128, 256, 131, 127, "rows"),
+    (1, 256, 32, 467, 300, "rows"), (1, 64, 64, 568, 568, "rows"), (4, 256, 256, 160, 160, "rows"),
+    (1, 64, 256, 116, 109, "small"), (1, 256, 256, 129, 124, "small"), (4, 256, 32, 150, 202, "small"),
+    (2, 256, 256, 75, 75, "small"), (8, 256, 512, 32, 32, "small"),
+])
+def test_f4_tap_gemm(n, cin, cout, h, w, gemm):
+    for layout in (W.NCHW, W.NHWC):
+        k = _kernels(4, n, cin, cout, h, w, layout)
+        assert (k["launches"], k["gemm"]) == (2, gemm), k
+
+
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+def test_small_kernel_on_many_narrow_blocks(layout):
+    """Few output channels, as many 64 x 64 blocks as used to go to the
+    row-streamed kernel: the small-layer kernel's 32 x 32 blocks at one per
+    compute unit, ragged in channels and tiles."""
+    torch_dev()
+    n, cin, cout, h, w = 3, 70, 27, 207, 201
+    x, f, b = workloads.random_case(53, n, cin, cout, h, w, signed=True)
+    eb = tapwise.calibrate_input_exps(x, m=4)
+    op = tapwise.make_plan(f, eb, bias=b, out_shift=10, relu=True, m=4)
+    gp = W.wino_f4_plan(f, eb, bias=b, out_shift=10, relu=True)
+    k = W.wino_probe_conv_kernels(gp, 0, n, h, w, layout)
+    assert (k["gemm"], k["co"], k["tiles"]) == ("small", 32, 32), k
+    assert (run_conv(gp, x, layout) == tapwise.conv_int8(x, op)).all()
