@@ -311,3 +311,41 @@ def test_i10_is_more_accurate_than_int8():
         y = tapwise.assemble(tapwise.output_transform(mm.cpu().numpy().astype(np.int64), info["sh"]), n, h, w)
         errs[bits] = np.sqrt(np.mean((y * 2.0 ** info["e_o"] - ref) ** 2))
     assert errs[10] < 0.5 * errs[8]
+
+
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+@pytest.mark.parametrize("cin,epi", [(64, 32), (90, 32), (90, 64), (128, 32), (128, 64), (192, 64)])
+def test_i10_operands_at_the_rails(cin, epi, layout):
+    """Whole pairs of k rows (64 channels) with both operands at the 10-bit rails,
+    where one fp32 accumulation reaches 64 * 2^18 = 2^24 or an odd sum just below
+    it.  Constant channels excite tap (1, 1) alone inside the image, with
+    V = 36 x, and nine equal weights give U = w / 4 there; tap (1, 1) reaches every
+    output once, so a bias of -M plus a small number shows M's lowest bit at
+    out_shift 0.  epi 32: the other taps' weights round to zero."""
+    torch_dev()
+    rng = np.random.default_rng(77 + cin)
+    n, cout, h, w = 1, 70, 13, 18
+    vq = np.where(rng.random(cin) < 0.3, 511, -512)
+    vq[:64] = -512
+    vq[[5, 40]] = 511                                        # an odd product in each row of the first pair
+    uq = np.where(rng.random((cout, cin)) < 0.5, 511, -512)
+    uq[:, :64] = np.where(vq[:64] == 511, 511, -512)         # all products positive: the largest sums
+    uq[0] = -512
+    uq[1] = np.where(vq == 511, -512, 511)                   # all negative
+    uq[2, :64] = np.where(np.arange(64) == 40, 511, -512)
+    x = np.broadcast_to(np.where(vq == 511, 15, -15).astype(np.int8)[None, :, None, None], (n, cin, h, w)).copy()
+    f = np.broadcast_to(4.0 * uq[:, :, None, None], (cout, cin, 3, 3)).astype(np.float32).copy()
+    m11 = uq.astype(np.int64) @ vq.astype(np.int64)
+    assert np.abs(uq[:, :64].astype(np.int64) @ vq[:64]).max() > 2 ** 24 - 2 ** 11
+    bias = (-m11 + rng.integers(-100, 101, cout)).astype(np.int32)
+    eg = [0 if t == 7 else 2 if epi == 64 else 20 for t in range(36)]
+    op = tapwise.make_plan(f, [0] * 36, e_g=eg, bias=bias, out_shift=0, bits=10)
+    ref = tapwise.conv_int8(x, op)
+    inside = ref[:, :, 4:8, 4:12] if epi == 32 else ref[:, :, 4:8, 4:8]
+    assert (inside == (m11 + bias)[None, :, None, None]).all()          # the oracle sees M's low bits too
+    for kind in (W.TAP_AUTO, W.TAP_RESIDENT):
+        gp = W.wino_f4_plan_i10(f, [0] * 36, w_exp=eg, bias=bias, out_shift=0)
+        assert W.wino_f4_plan_info(gp)["epilogue_bits"] == epi
+        W.wino_f4_plan_set_tap_kernel(gp, kind)
+        got = run_conv(gp, x, layout)
+        assert (got == ref).all(), f"kernel {kind}: {(got != ref).sum()} mismatches"
