@@ -4,13 +4,13 @@ power-of-two quantization on one MI355X.
 
 One step = one pass of the whole online path over one batch: input transform
 with tap-wise requant (K1) and the 36-tap int8 MFMA GEMM with the fused
-output transform, bias and requant (K2), i.e. one wino_f4_conv_int8 call.
-Inputs are resident in HBM before the timed region.  The default workload is
+output transform, bias and requant (K2), i.e. one wino_f4_conv_int8 call (small
+layers: one launch for both).  Inputs are resident in HBM before the timed region.  The default workload is
 the largest layer (N=4, 256->256, 160x160, NHWC), the configuration the
 tap-GEMM MFMA-utilisation target refers to.
 
 Printed on one JSON line: the contract fields, the roofline of the dominant
-kernel (durations from HIP events on the launch stream), both kernels'
+kernel (durations from HIP events on the launch stream), the kernels'
 figures, the direct int8 convolution of the same library on the same layer
 (speed-up), and the CPU oracle timed on a bounded sample.
 """
@@ -455,50 +455,54 @@ def main():
         W.wino_f4_conv_int8(plan, xd, y, n, h, w, layout, variant, ws if variant == W.SPLIT else None)
 
     # per-kernel durations: each of the two launches of a step timed on its
-    # own (HIP events on the launch stream), see kernel_ms
+    # own (HIP events on the launch stream), see kernel_ms; where the step is
+    # one launch, that one, and the two launches beside it as another route
     th, tw = (h + mt - 1) // mt, (w + mt - 1) // mt
     T = n * th * tw
     ntap = (mt + 2) ** 2
     lay = 1 if layout == W.NHWC else 0
-    choice = W.wino_f4_tap_kernel_choice(plan, n, h, w)
-    rows = choice in (W.TAP_ROWS, W.TAP_ROWS_STREAMK)   # the same kernel, split or not
-    # kernel names as the profiler shows them (template arguments included;
-    # the tap-resident kernel's block configuration is a class argument)
+    kern = W.wino_probe_conv_kernels(plan, xd, n, h, w, layout)
+    one_launch = variant == W.SPLIT and kern["launches"] == 1
+    # the two launches of the split calls: an odd address never takes the one launch
+    two = W.wino_probe_conv_kernels(plan, 1, n, h, w, layout) if one_launch else kern
+    # kernel names as the profiler shows them (template arguments included; the
+    # tap-resident kernel's block configuration is a class argument).
     # the one-instruction requantization serves plans whose e_B are all <= 16 - bits
-    k1_sat = "true" if all(0 <= e <= 16 - args.bits for e in eb) else "false"
+    sat = "true" if all(0 <= e <= 16 - args.bits for e in eb) else "false"
     if layout == W.NHWC and cin >= 4:
-        # NHWC: the transform reads global memory directly
         # tiles per block: 8 unless 16 leaves fewer idle tiles per row
-        twt = (w + mt - 1) // mt
-        k1_tx = 8 if (-twt) % 8 <= (-twt) % 16 else 16
-        k1_name, k1_inst = "wino_input_xform_nhwc", f"wino_input_xform_nhwc<{mt},{args.bits},{k1_tx},{k1_sat}>"
+        k1_tx = 8 if (-tw) % 8 <= (-tw) % 16 else 16
+        k1_name, k1_inst = "wino_input_xform_nhwc", f"wino_input_xform_nhwc<{mt},{args.bits},{k1_tx},{sat}>"
     else:
-        twt = (w + mt - 1) // mt
-        k1_tx = 8 if layout == W.NCHW and (-twt) % 8 < (-twt) % 16 else 16
-        k1_name, k1_inst = "wino_input_xform", f"wino_input_xform<{mt},{lay},{args.bits},{k1_tx},{k1_sat}>"
-    if rows and args.bits == 10:
+        k1_name, k1_inst = "wino_input_xform", f"wino_input_xform<{mt},{lay},{args.bits},{two['xform_tiles']},{sat}>"
+    gemm = two["gemm"]
+    if gemm == "rows_wide":
         k2_name = "wino_tap_gemm_rows_wide"
         k2_inst = f"wino_tap_gemm_rows_wide<{lay},10,{'int' if info['epilogue_bits'] == 32 else 'longlong'}>"
-    elif choice == W.TAP_ROWS_STREAMK:
+    elif gemm == "rows_streamk":
         k2_name, k2_inst = "wino_tap_gemm_rows_sk", f"wino_tap_gemm_rows_sk<{lay}>"
-    elif rows:
-        k2_name, k2_inst = "wino_tap_gemm_rows", "wino_tap_gemm_rows<RwCfg<%s>,%d,%s>" % (("32,3,4", lay, "true,0") if cin <= 64 else ("64,6,3", lay, "false,0"))
-    elif choice == W.TAP_WAVES:
+    elif gemm == "rows":
+        cfg = "32,3,4" if two["tiles"] == 32 else "64,6,3"
+        k2_name, k2_inst = "wino_tap_gemm_rows", f"wino_tap_gemm_rows<RwCfg<{cfg}>,{lay},{'true' if cin <= 64 else 'false'},0>"
+    elif gemm == "waves":
         # 64-channel chunks per ring stage: the largest of 4, 3, 2, 1 dividing the padded chunks
         nkc = (cin + 63) // 64
         nk = next(k for k in (4, 3, 2, 1) if nkc % k == 0)
         k2_name, k2_inst = "wino_tap_gemm_ws", f"wino_tap_gemm_ws<{lay}, {nk}>"
-    elif args.tap_kernel == "auto" and args.bits == 8 and info["epilogue_bits"] == 32:
-        # its block shape depends on the layer: 2,2 / 1,2 / 1,1 sixteens of channels and tiles
-        k2_name, k2_inst = "wino_tap_gemm_small", f"wino_tap_gemm_small<{mt},"
+    elif gemm == "small":
+        k2_name = "wino_tap_gemm_small"
+        k2_inst = f"wino_tap_gemm_small<{mt},{two['co'] // 16},{two['tiles'] // 16},{lay},0>"
     else:
         k2_name, k2_inst = "wino_tap_gemm", f"wino_tap_gemm<{mt},{lay},{info['epilogue_bits']},0,{args.bits}>"
+    cs_name, cs_inst = "wino_conv_small", f"wino_conv_small<{mt},{kern['co'] // 16},{lay},{sat}>"
     k1_ms = k2_ms = None
     if variant == W.SPLIT:
         k1 = lambda: W.wino_f4_input_transform(plan, xd, n, h, w, layout, ws)
         k2 = lambda: W.wino_f4_tap_gemm(plan, ws, y, n, h, w, layout)
         k1_ms, k1_p10, k1_p90 = kernel_ms(torch, k1, max(args.steps, 50))
         k2_ms, k2_p10, k2_p90 = kernel_ms(torch, k2, max(args.steps, 50))
+        if one_launch:
+            cs_ms, cs_p10, cs_p90 = kernel_ms(torch, step, max(args.steps, 50))
 
     # the timed steps: W warmup steps, then exactly K steps back to back.  They
     # run after the per-kernel timings, which keep the GPU busy for a few ms
@@ -532,11 +536,11 @@ def main():
     # must move (x, y, Uq, bias) and the SPLIT path's extra Vq round trip
     fused_min = n * h * w * cin + n * h * w * cout + eb_bytes * ntap * cin * cout + 4 * cout
     split_bytes = fused_min + 2 * eb_bytes * ntap * T * cin
-    layer_hbm = {"alg_bytes_min": fused_min, "alg_bytes_split": split_bytes,
-                 "GB/s_split": split_bytes / (ms * 1e-3) / 1e9,
-                 "frac_split": split_bytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                 "frac_min": fused_min / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
-    kernels = {}
+    layer_hbm = {"alg_bytes_min": fused_min, "frac_min": fused_min / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
+    if not one_launch:                                          # no Vq in memory in the one launch
+        layer_hbm.update({"alg_bytes_split": split_bytes, "GB/s_split": split_bytes / (ms * 1e-3) / 1e9,
+                          "frac_split": split_bytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS})
+    kernels, two_launches = {}, None
     cfg_tag = args.config + (f"L{args.layer}" if args.layer else "") + ("_i10" if args.bits == 10 else "")
     if k1_ms is not None:
         kernels[k1_name] = {"ms": k1_ms, "p10_ms": k1_p10, "p90_ms": k1_p90, "bound": "hbm", "bytes": k1_bytes,
@@ -548,7 +552,7 @@ def main():
                             "frac": tap_ops / (k2_ms * 1e-3) / 1e12 / k2_peak,
                             "GB/s_algorithmic": k2_bytes / (k2_ms * 1e-3) / 1e9,
                             "traffic_bytes": counter_traffic(cfg_tag, args.layout, k2_inst, args.transform),
-                            "stream_k": choice == W.TAP_ROWS_STREAMK}
+                            "stream_k": gemm == "rows_streamk"}
         # the input transform's HBM figures are taken cold (inputs in HBM,
         # caches flushed): warm, C5's 26 MB input sits in the 256 MB MALL
         k1c = cold["kernels_ms"][k1_name]
@@ -556,7 +560,19 @@ def main():
                                  "cold_ms": k1c, "GB/s": k1_bytes / (k1c * 1e-3) / 1e9,
                                  "frac": k1_bytes / (k1c * 1e-3) / 1e9 / PEAK_HBM_GBS})
         kernels[k2_name]["cold_ms"] = cold["kernels_ms"][k2_name]
-        if k2_ms >= k1_ms:
+        if one_launch:
+            # the step runs this kernel alone; K1 and K2 above are what
+            # wino_f4_input_transform and wino_f4_tap_gemm would run
+            two_launches, kernels = kernels, {cs_name: {
+                "ms": cs_ms, "p10_ms": cs_p10, "p90_ms": cs_p90, "cold_ms": cold["step_ms"], "bound": "mfma",
+                "ops": tap_ops, "TOP/s": tap_ops / (cs_ms * 1e-3) / 1e12,
+                "frac": tap_ops / (cs_ms * 1e-3) / 1e12 / k2_peak,
+                "GB/s_algorithmic": fused_min / (cs_ms * 1e-3) / 1e9,
+                "traffic_bytes": counter_traffic(cfg_tag, args.layout, cs_inst, args.transform)}}
+            roofline = {"kernel": cs_name, "bound": "mfma", "achieved": kernels[cs_name]["TOP/s"],
+                        "peak": k2_peak, "unit": k2_unit, "frac": kernels[cs_name]["frac"],
+                        "traffic": kernels[cs_name]["traffic_bytes"]}
+        elif k2_ms >= k1_ms:
             roofline = {"kernel": k2_name, "bound": "mfma", "achieved": kernels[k2_name]["TOP/s"],
                         "peak": k2_peak, "unit": k2_unit, "frac": kernels[k2_name]["frac"],
                         "traffic": kernels[k2_name]["traffic_bytes"]}
@@ -601,8 +617,10 @@ def main():
     measured["hbm_copy_GBs"] = 2.0 * src.numel() / (best * 1e-3) / 1e9
     del src, dst
     if variant == W.SPLIT and args.bits == 8:
-        kernels[k2_name]["frac_of_measured_32x32x32"] = kernels[k2_name]["TOP/s"] / measured["int8_mfma_32x32x32_TOPS"]
-        kernels[k1_name]["frac_of_measured_copy"] = kernels[k1_name]["GB/s"] / measured["hbm_copy_GBs"]
+        split_kernels = two_launches or kernels
+        split_kernels[k2_name]["frac_of_measured_32x32x32"] = (split_kernels[k2_name]["TOP/s"] /
+                                                               measured["int8_mfma_32x32x32_TOPS"])
+        split_kernels[k1_name]["frac_of_measured_copy"] = split_kernels[k1_name]["GB/s"] / measured["hbm_copy_GBs"]
 
     direct = None
     if not args.no_direct:
@@ -648,6 +666,7 @@ def main():
         "roofline": roofline,
         "bitexact": bitexact,
         "kernels": kernels,
+        "two_launches_not_in_step": two_launches,
         "tap_gemm_mfma_frac_of_step": tap_ops / (ms * 1e-3) / 1e12 / k2_peak,
         "layer_hbm": layer_hbm,
         "cold": {"step_ms": cold["step_ms"], "TOPS": direct_ops / (cold["step_ms"] * 1e-3) / 1e12,
