@@ -54,7 +54,9 @@ typedef enum wino_status {
 typedef enum wino_layout { WINO_NCHW = 0, WINO_NHWC = 1 } wino_layout;
 
 /* SPLIT: input transform to a tap-major int8 workspace, then the tap GEMM
- * with the output transform fused into its epilogue (two launches).
+ * with the output transform fused into its epilogue: two launches, or on small
+ * layers one that keeps the transformed tiles in LDS (the workspace is then
+ * required but left alone).
  * FUSED: one launch; the input transform runs in the GEMM prologue and no
  * workspace is used.                                                        */
 typedef enum wino_variant { WINO_SPLIT = 0, WINO_FUSED = 1 } wino_variant;
@@ -155,12 +157,16 @@ wino_status wino_f4_plan_set_tap_kernel(wino_f4_plan_t plan, int32_t kind);
  * wino_select_algorithm -- per-layer choice between the two Winograd
  * transforms and direct convolution (the paper's point that the best
  * algorithm depends on the layer, Sec. V: F2 for small spatial sizes, F4 for
- * large ones).  Host only, no device work; a fixed rule from measurements on
- * MI355X: DIRECT for NHWC layers below 2^27 direct-equivalent operations
- * (there the two Winograd launches cost more than the whole direct
- * convolution; in NCHW the direct convolution runs a simple kernel that F2
- * beats, so NCHW never gets DIRECT); F4 when its 64x64 row-streamed blocks,
- * (Cout/64) x (tiles/64), fill the device's compute units; F2 otherwise.
+ * large ones).  Host only, no device work; a fixed rule: DIRECT for NHWC layers
+ * below 2^27 direct-equivalent operations; F4 when its 64x64 row-streamed
+ * blocks, (Cout/64) x (tiles/64), fill the device's compute units; F2
+ * otherwise (in NCHW the direct convolution of small layers runs a simple
+ * kernel that F2 beats, so NCHW never gets DIRECT).  The three give different
+ * results, so the lines stay where they were drawn, when both Winograd paths
+ * took two launches at every size.  By today's times a new program does better
+ * with F2 where the rule says DIRECT (2.3 times as fast in the mean of 73 NHWC
+ * layers below the line, on every one), and with F4 on many layers below the
+ * F4 line (1x64->64 300x500 NHWC: F4 19 us, F2 26).
  *   layout: the activations' layout.
  *   algo:   host int32 out, one of wino_algo.
  * Errors: WINO_EINVAL (null algo, sizes < 0, channels < 1, unknown layout).
@@ -172,7 +178,8 @@ wino_status wino_select_algorithm(int32_t n, int32_t cin, int32_t cout, int32_t 
 /*
  * wino_f4_tap_kernel_choice -- the tap-GEMM kernel (WINO_TAP_ROWS, WINO_TAP_WAVES
  * or one of the WINO_TAP_RESIDENT_* shapes) that a SPLIT wino_f4_conv_int8 runs for an
- * n x h x w input, under the plan's wino_f4_plan_set_tap_kernel setting.
+ * n x h x w input, under the plan's wino_f4_plan_set_tap_kernel setting.  Under AUTO
+ * RESIDENT_64X32 also stands for the small-layer kernels (wino_tap_kernel above).
  * Host only, no device work.  kind: host int32 out.
  * Errors: WINO_EINVAL (null plan or kind, negative sizes), WINO_EUNSUPPORTED
  * (sizes beyond the library's limits).
@@ -261,9 +268,9 @@ wino_status wino_f2_plan_int8(wino_f4_plan_t* out, const int8_t* w_oihw_dev, int
  * [ntap][ntiles][cin], each an exact 10-bit integer).  wino_f4_plan_info
  * returns its exponents and epilogue width; its uq argument must be NULL
  * (WINO_EINVAL otherwise).  The tap GEMM runs on fp16 matrix cores: the
- * 10-bit integers are exact in fp16 and each 32-channel partial sum is an
- * integer below 2^24, exact in the fp32 accumulator, before it is added to
- * the int32 (or int64) accumulation -- the result is bit-exact.
+ * 10-bit integers are exact in fp16 and each partial sum of 32 or 64 channels is
+ * an integer of at most 2^24, exact in the fp32 accumulator, before it is added to
+ * the int32 accumulation -- the result is bit-exact.
  */
 wino_status wino_f4_plan_i10(wino_f4_plan_t* out, const float* w_oihw, int32_t cin, int32_t cout,
                              const int8_t* in_exp, const int8_t* w_exp, const int32_t* bias, int32_t out_shift,
@@ -359,9 +366,10 @@ wino_status wino_f4_conv_int8_noalloc(wino_f4_plan_t plan, const int8_t* x, int8
                                       int32_t h, int32_t w, wino_layout layout, hipStream_t stream);
 
 /*
- * The two launches of the SPLIT variant as separate calls, for callers that
- * schedule or time them individually; wino_f4_conv_int8(SPLIT) equals
- * wino_f4_input_transform followed by wino_f4_tap_gemm on the same stream.
+ * The SPLIT variant as two separate launches, for callers that schedule or time
+ * them individually; wino_f4_conv_int8(SPLIT) gives the same y as
+ * wino_f4_input_transform followed by wino_f4_tap_gemm on the same stream
+ * (small layers run neither: one launch does both).
  * wino_f4_input_transform: x -> workspace (Vq, the tap-major int8
  *   Winograd-domain input: B^T d B and the tap-wise requantization).
  * wino_f4_tap_gemm: workspace -> y (the 36 tap GEMMs, alignment, A^T M A,

@@ -16,8 +16,8 @@
 //                         out_xform / dconv / write steps of the operator
 //                         dataflow, Sec. IV-B2).  wino_tap_gemm_rows
 //                         (wino_tap_rows.h) for large F4 layers,
-//                         wino_tap_gemm_small (wino_tap_small.h) for F2 and
-//                         small F4 ones.
+//                         wino_tap_gemm_small (wino_tap_small.h) for most F2
+//                         and small F4 ones, wino_tap_gemm for the rest.
 //   wino_conv_small       both in one launch for small layers
 //                         (wino_conv_small.h).
 //
@@ -57,7 +57,8 @@ struct K1Band {
 struct K1Args {
     int n, cin, h, w, th, tw, cin_pad;
     int ntxb, ncg;
-    int x_vec;                          // 16-byte loads allowed (Cin % 16 == 0, x aligned)
+    int x_vec;                          // NHWC band by 16-byte loads (Cin % 16 == 0, x aligned; only image
+                                        //   rows of 2 GiB and more get there, others load directly)
     int x_dw;                           // NCHW word loads allowed (W >= 4, image < 2 GiB)
     int vq_buf;                         // tap planes below 4 GiB: buffer stores with a scalar base
     long long t_pad;                    // tile stride of a tap plane in Vq
@@ -66,7 +67,7 @@ struct K1Args {
     uint32_t rnd2[kTaps];               // 2^(e_B - 1) (0 for e_B = 0) in both 16-bit halves
     int q_sat;                          // every e_B <= 16 - Q: one-instruction requantization
     int* sk_cnt;                        // stream-K counters of the tap GEMM that follows, zeroed
-    int sk_ncnt;                        //   by workgroup 0 (MODE 0; none when sk_ncnt is 0)
+    int sk_ncnt;                        //   by workgroup 0 (none when sk_ncnt is 0)
 };
 
 // zero the stream-K counters of the tap GEMM that reads this Vq (workgroup 0)
@@ -1406,7 +1407,9 @@ int k1_direct_tx(int tw) {
     return idle8 <= idle16 ? 8 : 16;
 }
 
-// whether the direct NHWC kernel takes this input
+// whether the direct NHWC kernel takes this input (x at no multiple of four bytes
+// goes through the band: the loads would take any address, but with Cin % 4 == 0
+// that was not measured)
 bool k1_direct(const K1Args& a, wino_layout layout, const int8_t* x) {
     return layout == WINO_NHWC && a.cin >= 4 && ((uintptr_t)x & 3) == 0 && (long long)a.w * a.cin < 0x7ffffff0ll;
 }
@@ -2048,8 +2051,9 @@ extern "C" wino_status wino_select_algorithm(int32_t n, int32_t cin, int32_t cou
     const double ops = 2.0 * 9 * (double)n * h * w * (double)cin * cout;
     // direct only in NHWC: small NCHW layers (Cin not a multiple of 64, or
     // W not a multiple of 4) run the simple MFMA kernel, which F2 beats
-    // (C1: 12.3 against 31 us), and the NCHW tile kernel's byte transposes
-    // leave it behind the Winograd paths on the large layers
+    // (C1: 6.4 against 30 us), and the NCHW tile kernel's byte transposes
+    // leave it behind the Winograd paths on the large layers.  The lines are
+    // older than the small-layer kernels (see the declaration)
     if (ops < (double)(1 << 27) && layout == WINO_NHWC) {
         *algo = WINO_ALGO_DIRECT;
         return WINO_OK;

@@ -75,7 +75,7 @@ __device__ __forceinline__ uint32_t relu4(uint32_t w) {
     return w & ~(t | (t - (t >> 7)));
 }
 
-// the same for lanes 0-31 only (512 bytes)
+// lds_copy16_s for lanes 0-31 only (512 bytes)
 __device__ __forceinline__ void lds_copy16_half(const void* base, uint32_t lane_off,
                                                 __attribute__((address_space(3))) void* dst) {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
@@ -83,7 +83,6 @@ __device__ __forceinline__ void lds_copy16_half(const void* base, uint32_t lane_
                  "s"(base), "{m0}"(m0));
 }
 
-// ONE: a single 64-channel chunk (Cin <= 64)
 // maximum of zmax over the workgroup's W waves into *out, one atomic
 template <int W>
 __device__ __forceinline__ void block_max(uint32_t zmax, uint32_t* lds, unsigned long long* out) {
@@ -98,6 +97,7 @@ __device__ __forceinline__ void block_max(uint32_t zmax, uint32_t* lds, unsigned
     }
 }
 
+// ONE: a single 64-channel chunk (Cin <= 64).
 // MODE 0: store y.  MODE 1: max |Y + bias| into *aux (calibration).
 template <class C, int LAYOUT, bool ONE, int MODE>
 __global__ __launch_bounds__(C::THREADS, 2) void wino_tap_gemm_rows(

@@ -17,7 +17,9 @@
 //   * wave a then folds its row, z_a = (M'[a, :]) A (M' = M 2^sh), into LDS, and
 //     all waves apply the column pass Y = A^T z, requantize and store.
 // Every operand byte is read by 16 CB or 16 TB columns only, so large F4 layers
-// run the LDS-staged row-streamed kernel; F2 layers always run this one.
+// run the LDS-staged row-streamed kernel, and F2 layers the staged 64 x 32 blocks
+// where these need no more rounds or Vq lies beyond the caches (the rules at
+// launch).
 // Measured against the 64 x 32 blocks it replaces (kernel time, us): F4 8x32x32
 // 128->128 16.2 -> 5.6, 256->512 22.5 -> 13.6, 2x75x75 256->256 26.0 -> 16.2; F2
 // 8x56x56 64->64 6.1 -> 5.9, 8x14x14 256->256 10.0 -> 6.4, 8x112x112 64->64 19.8
