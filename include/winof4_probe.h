@@ -31,8 +31,8 @@ wino_status wino_probe_mfma_int8(int32_t shape, int32_t iters, int32_t blocks, i
 
 /*
  * wino_probe_conv_kernels -- the kernels that a SPLIT wino_f4_conv_int8 with
- * this plan launches for an n x h x w input x (only its address is looked at)
- * with a workspace of wino_f4_workspace_bytes.  Host only, no device work.
+ * this plan launches for an n x h x w input x (only its address is looked at),
+ * an output apart from it and a workspace of wino_f4_workspace_bytes.  Host only, no device work.
  * All fields are 0 for an empty input.  Errors: WINO_EINVAL (null plan or k,
  * negative sizes, unknown layout), WINO_EUNSUPPORTED (sizes beyond the
  * library's limits).

@@ -1968,9 +1968,13 @@ wino_status launch_conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_l
 //   14.2, a single channel block from b 1.5 on 1x96->64 169x163 12.8 / 16.6; 3 chunks
 //   10.0 / 9.7, 2x192->192 42x36 18.1 / 11.7; 8 chunks 20.3 / 11.1.  F4: 1 chunk
 //   10.0 / 10.8, 2 15.3 / 11.8.
+// A y that overlaps x is ruled out by the interface, but in two launches x is read
+// before y is written; here blocks would read what others have overwritten.
 // Returns the block's channels in sixteens, 0: not taken.
-int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x) {
+int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, const int8_t* y) {
     if (p->bits != 8 || p->epi_bits != 32 || p->tap_kernel != WINO_TAP_AUTO) return 0;
+    const uintptr_t xa = (uintptr_t)x, ya = (uintptr_t)y, px = (uintptr_t)g.n * g.h * g.w;
+    if (y && xa < ya + px * p->cout && ya < xa + px * p->cin) return 0;
     const long long xb = (long long)g.n * g.h * g.w * p->cin;
     if (xb >= 0x7ffffff0ll || (layout == WINO_NHWC ? p->cin < 4 : g.w < 4) || ((uintptr_t)x & 3) != 0) return 0;
     const long long cus = num_cus(), tb = (g.ntiles + 15) / 16;
@@ -1992,7 +1996,7 @@ int one_launch_cb(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout
 
 bool conv_small(const wino_f4_plan_s* p, const Geometry& g, wino_layout layout, const int8_t* x, int8_t* y,
                 hipStream_t stream, wino_status& st) {
-    const int cb = one_launch_cb(p, g, layout, x);
+    const int cb = one_launch_cb(p, g, layout, x, y);
     if (cb == 0) return false;
     CsArgs a;
     a.k = k2_args(p, g, layout, y);
@@ -2137,7 +2141,7 @@ extern "C" wino_status wino_probe_conv_kernels(wino_f4_plan_t p, const int8_t* x
     if (st != WINO_OK) return st;
     *k = {};
     if (g.ntiles == 0) return WINO_OK;
-    if (const int cb = one_launch_cb(p, g, layout, x)) {
+    if (const int cb = one_launch_cb(p, g, layout, x, nullptr)) {
         *k = {1, WINO_PROBE_XFORM_NONE, 0, WINO_PROBE_GEMM_SMALL, 16 * cb, 16};
         return WINO_OK;
     }

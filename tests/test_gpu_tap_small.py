@@ -102,6 +102,28 @@ def test_one_launch_convolution(shape, m, layout):
     assert (y == ref).all(), f"{(y != ref).sum()} mismatches"
 
 
+@pytest.mark.parametrize("layout", [W.NCHW, W.NHWC])
+@pytest.mark.parametrize("m", [4, 2])
+def test_output_over_the_input(m, layout):
+    """A layer of the one launch's sizes whose output overlaps its input, wholly or in
+    part: two launches, which read x before they write y, as before that kernel."""
+    torch = torch_dev()
+    n, c, h, w = 4, 48, 24, 28
+    x, f, b = workloads.random_case(35, n, c, c, h, w, signed=True)
+    eb = tapwise.calibrate_input_exps(x, m=m)
+    op = tapwise.make_plan(f, eb, bias=b, out_shift=9, m=m)
+    gp = (W.wino_f4_plan if m == 4 else W.wino_f2_plan)(f, eb, bias=b, out_shift=9)
+    xd, ref = to_device(x, layout).reshape(-1), tapwise.conv_int8(x, op)
+    ws = workspace(gp, n, h, w)
+    for off in (0, 4, xd.numel() - 4):
+        buf = torch.zeros(xd.numel() + off, dtype=torch.int8, device="cuda")
+        buf[:xd.numel()] = xd
+        assert W.wino_probe_conv_kernels(gp, buf, n, h, w, layout)["launches"] == 1
+        W.wino_f4_conv_int8(gp, buf[:xd.numel()], buf[off:], n, h, w, layout, W.SPLIT, ws)
+        y = buf[off:].reshape((n, c, h, w) if layout == W.NCHW else (n, h, w, c))
+        assert (from_device_nchw(y, layout) == ref).all(), off
+
+
 def test_f2_wide_blocks():
     """The F2 sizes that keep the 64x32 tap-resident blocks under AUTO."""
     torch = torch_dev()
