@@ -39,11 +39,13 @@ def test_input_words(shape, m, layout):
     assert e == tapwise.calibrate_input_exps(x, m=m)
 
 
-@pytest.mark.parametrize("shape", [(3, 70, 40, 9, 13), (1, 40, 70, 57, 62), (2, 140, 130, 150, 152), (4, 33, 150, 97, 95)])
+@pytest.mark.parametrize("shape", [(3, 70, 40, 9, 13), (1, 40, 70, 57, 62), (2, 140, 130, 150, 152), (4, 33, 150, 97, 95),
+                                   (2, 130, 310, 52, 45)])
 @pytest.mark.parametrize("m", [4, 2])
 def test_output_maximum(shape, m):
-    """calibrate_output on the row-streamed kernel's two block shapes and the
-    small-layer kernel's: the maximum counts in-image outputs only."""
+    """calibrate_output on the row-streamed kernel's two block shapes, the
+    small-layer kernel's and (F2, last shape) the 64 x 32 blocks: the maximum counts
+    in-image outputs only."""
     n, cin, cout, h, w = shape
     x, f, b = workloads.random_case(43, n, cin, cout, h, w, signed=True)
     eb = tapwise.calibrate_input_exps(x, m=m)
